@@ -84,6 +84,31 @@ struct C2RArgs {
   int bgroup;
 };
 
+// Transforms of 1-D fp16 signals (fno_line.hip): S = planes signals of N
+// samples, spectrum [S][Kb].
+struct LineArgs {
+  const void* in;
+  void* out;
+  const void* x;      // inverse: epilogue input or null
+  // forward: [2*Kbp][128] cos, -sin of 2 pi k m / N; inverse: [N up to a
+  // multiple of 128][2*Kbp], columns 2 k and 2 k + 1: cos, -sin of 2 pi k n / N
+  const void* tw;
+  const void* rowph;  // forward: fp32 (cos, sin) of 2 pi k 128 r / N, [32][Kbp]
+  const void* blkph;  // forward: fp32 (cos, sin) of 2 pi k 4096 b / N, [17][Kbp]
+  const void* lut;    // fp16 f(x) of every non-negative fp16 code (f odd)
+  int lut_sat;        // first code from which f stays at its +inf value
+  int64_t planes;
+  int N, Kb;
+  float scale;
+  int act;            // forward: pre-activation applied (ACT_NONE: none); inverse: of the epilogue
+  float clip;
+  int lw;             // forward: 1 << lw waves per signal (set by the launcher)
+  int rtg;            // inverse: row tiles per work-group (set by the launcher)
+};
+// hipErrorNotSupported: not a shape of this path.  nct = 2 Kbp / 16, nkv = 2 Kbp / 32.
+hipError_t launch_r2c_line(const LineArgs& a, int nct, int num_cu, hipStream_t s);
+hipError_t launch_c2r_line(const LineArgs& a, int nkv, int num_cu, hipStream_t s);
+
 // Clip bounds of the statistics-based pre-activation: for each of `groups`
 // contiguous groups of n values of x (fp16 or fp32), mean -/+ k population
 // standard deviations, in double (NaN when not finite).

@@ -356,6 +356,7 @@ struct DevTables {
   int actSat = 0, gradSat = 0;  // first codes of the saturated tails (fp16 plans)
   const void *eFr, *eFi, *eIr, *eIi;
   const void *twA2, *cB2, *sB2, *cI2, *sI2, *twI2;  // radix-2 wide-plane tables
+  const void *lnF, *lnRow, *lnBlk, *lnI;            // 1-D fp16 signals
 };
 
 struct Plan {
@@ -641,6 +642,39 @@ void fill_tables(const fno_conv_desc* d, const Geo& g, std::vector<T>& buf,
         }
       }
   }
+  if (nd == 1 && g.elem == ELEM_F16) {
+    // 1-D signals (LineArgs): forward twiddles of 128 samples, fp32 phases of
+    // the rows and blocks, inverse twiddles with (re, im) columns interleaved
+    auto fp32 = [&](size_t at, size_t i, double c, double sn) {
+      const float v[2] = {(float)c, (float)sn};
+      std::memcpy(&buf[at + 4 * i], v, 8);
+    };
+    size_t lf = alloc((size_t)2 * g.Kbp * 128);
+    size_t lr = alloc((size_t)4 * 32 * g.Kbp), lb = alloc((size_t)4 * 17 * g.Kbp);
+    const int np = (int)round_up(g.Nb, 128);
+    size_t li = alloc((size_t)np * 2 * g.Kbp);
+    for (int t = 0; t < g.Kb; ++t) {
+      double cv, sv;
+      for (int m = 0; m < 128; ++m) {
+        twiddle(t, m, g.Nb, &cv, &sv);
+        buf[lf + (size_t)t * 128 + m] = (T)cv;
+        buf[lf + (size_t)(g.Kbp + t) * 128 + m] = (T)(-sv);
+      }
+      for (int r = 0; r < 32; ++r) {
+        twiddle(t, (int64_t)128 * r, g.Nb, &cv, &sv);
+        fp32(lr, (size_t)r * g.Kbp + t, cv, sv);
+      }
+      for (int b = 0; b < 17; ++b) {
+        twiddle(t, (int64_t)4096 * b, g.Nb, &cv, &sv);
+        fp32(lb, (size_t)b * g.Kbp + t, cv, sv);
+      }
+      for (int n = 0; n < g.Nb; ++n) {
+        twiddle(t, n, g.Nb, &cv, &sv);
+        buf[li + (size_t)n * 2 * g.Kbp + 2 * t] = (T)cv;
+        buf[li + (size_t)n * 2 * g.Kbp + 2 * t + 1] = (T)(-sv);
+      }
+    }
+  }
   if (nd == 3) {
     const int64_t m1 = d->modes[0];
     // forward E[t][l] = exp(-2 pi i k1(t) l / N1): [Lout16_f][Linp_f]
@@ -764,6 +798,12 @@ fno_status build_tables(const fno_conv_desc* d, Plan* pl) {
     pl->t.sB2 = at(18);
     pl->t.cI2 = at(19);
     pl->t.sI2 = at(20);
+  }
+  if (pl->g.nd == 1 && pl->g.elem == ELEM_F16) {
+    pl->t.lnF = at(15);
+    pl->t.lnRow = at(16);
+    pl->t.lnBlk = at(17);
+    pl->t.lnI = at(18);
   }
   if (pl->g.nd == 3) {
     pl->t.eFr = at(15);
@@ -1060,6 +1100,24 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
   a.lut = pl->t.lutAct;
   if (a.planes > 0x7fffffff || (g.nd == 3 && g.B * C > 65535)) return FNO_ERR_UNSUPPORTED;
   bool done = sigma;
+  if (!done && g.elem == ELEM_F16 && g.nd == 1) {
+    LineArgs l{};
+    l.in = in;
+    l.out = spec;
+    l.tw = pl->t.lnF;
+    l.rowph = pl->t.lnRow;
+    l.blkph = pl->t.lnBlk;
+    l.lut = pl->t.lutAct;
+    l.lut_sat = pl->t.actSat;
+    l.planes = a.planes;
+    l.N = g.Nb;
+    l.Kb = g.Kb;
+    l.scale = a.scaleA;
+    l.act = a.act;
+    hipError_t e = timed(kname, s, [&] { return launch_r2c_line(l, g.nct, pl->num_cu, s); });
+    if (e == hipSuccess) done = true;
+    else if (e != hipErrorNotSupported) return hip_fail(e, kname);
+  }
   if (!done && g.elem == ELEM_F16 && a.vec && g.Kb % 4 == 0 && g.Nb <= 256 && g.Na <= 128) {
     const int nka = g.Nbp / 32, ntb = g.Kbp / 16, nta = g.Kap16 / 16;
     const size_t lds = r2c_chain_lds_bytes(nka, ntb, nta, g.NaC, do_tanh);
@@ -1196,6 +1254,22 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     a.bgroup = g.nd == 3 ? g.N1 : 1;
     FNO_HIP(timed(kname, s, [&] { return launch_c2r(g.elem, g.nct, a, c2r_lds_bytes(g.elem, g.Kbp, g.Kap, g.R_i), s); }));
     return FNO_OK;
+  }
+  if (g.elem == ELEM_F16 && g.nd == 1) {
+    LineArgs l{};
+    l.in = spec;
+    l.out = out;
+    l.x = x_epi;
+    l.tw = pl->t.lnI;
+    l.planes = a.planes;
+    l.N = g.Nb;
+    l.Kb = g.Kb;
+    l.scale = scale;
+    l.act = g.act;
+    l.clip = g.clip;
+    hipError_t e = timed(kname, s, [&] { return launch_c2r_line(l, g.nct / 2, pl->num_cu, s); });
+    if (e == hipSuccess) return FNO_OK;
+    if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
   if (g.elem == ELEM_F16 && g.Nb % 16 == 0 && g.Kb % 4 == 0 && g.Nb <= 256 && g.Na <= 128) {
     const int ng = g.Nb64 / 64, ntb = g.Kbp / 16, nkz = g.Kap / 32;
