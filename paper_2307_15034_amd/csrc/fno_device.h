@@ -108,6 +108,27 @@ __device__ __forceinline__ float preact_grad_f32(float x, int act, float clip) {
   return 1.0f - t * t;
 }
 
+// v[e] *= f'(x[e]) in fp32 for eight fp16 inputs: tanh's derivative as
+// 4 e / (1 + e)^2 with e = exp(-2|x|) (no cancellation, half the instructions
+// of 1 - tanh^2; relative error below 4e-7 against the 5e-4 of the fp16
+// result).  One branch on the kind for the eight.
+__device__ __forceinline__ void mul_preact_grad8(float (&v)[8], const h8& x, int act, float clip) {
+  if (act == 2) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float ax = __builtin_fabsf((float)x[e]);
+      v[e] *= ax <= clip ? 1.0f : (ax > clip ? 0.0f : ax);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float t = __builtin_amdgcn_exp2f(__builtin_fabsf((float)x[e]) * -2.8853900817779268f);
+      const float r = __builtin_amdgcn_rcpf(1.0f + t);
+      v[e] *= (4.0f * t) * (r * r);
+    }
+  }
+}
+
 // The statistics-based clip (act 3) with its plane's bounds [lo, hi],
 // compared in double; NaN bounds (a plane with a non-finite value) give NaN.
 __device__ __forceinline__ float preact_sigma_f32(float x, double lo, double hi) {
@@ -419,11 +440,31 @@ __host__ __device__ __forceinline__ int lutn_bytes(int sat) {
   return ((sat + 1 + LUTN_NANS) * 2 + 255) & ~255;
 }
 
-// Stage tab[0..sat] of a global table and the NaN entries (NT threads).
+// n 16-byte pieces, piece i read from src(i) and written to dst(i), by NT
+// threads: U loads of a thread are in flight together, so a table costs one
+// memory latency per U NT pieces (a plain loop waits for each one).
+template <int NT, int U, typename Src, typename Dst>
+__device__ __forceinline__ void stage_pieces(int n, Src src, Dst dst) {
+  for (int i0 = threadIdx.x; i0 < n; i0 += NT * U) {
+    u32x4 v[U];
+#pragma unroll
+    for (int e = 0; e < U; ++e) v[e] = *src(min(i0 + e * NT, n - 1));
+#pragma unroll
+    for (int e = 0; e < U; ++e)
+      if (i0 + e * NT < n) *dst(i0 + e * NT) = v[e];
+  }
+}
+
+// Stage tab[0..sat] of a global table (16-byte aligned) and the NaN entries
+// (NT threads).
 template <int NT>
 __device__ __forceinline__ void stage_lutn(_Float16* dst, const void* src, int sat) {
   const _Float16* s = reinterpret_cast<const _Float16*>(src);
-  for (int i = threadIdx.x; i <= sat; i += NT) dst[i] = s[i];
+  const int full = (sat + 1) / 8;
+  stage_pieces<NT, 5>(
+      full, [&](int i) { return reinterpret_cast<const u32x4*>(s) + i; },
+      [&](int i) { return reinterpret_cast<u32x4*>(dst) + i; });
+  for (int i = full * 8 + threadIdx.x; i <= sat; i += NT) dst[i] = s[i];
   const uint16_t qnan = 0x7e00;
   for (int i = threadIdx.x; i < LUTN_NANS; i += NT) __builtin_memcpy(&dst[sat + 1 + i], &qnan, 2);
 }
@@ -507,11 +548,16 @@ __device__ __forceinline__ void rotate(f4& re, f4& im, const f2& cs) {
 
 // Eight halves at element row + col of a plane whose rows end at column n:
 // one 16-byte store, the last partial eight element by element.  Rows past
-// the plane fall outside its resource.
-__device__ __forceinline__ void store_tail8(const PlaneRef& p, int row, int col, int n,
+// the plane fall outside its resource.  The stores stream past the caches
+// where rows are whole 128-byte lines (nt: 512 x 512 planes, inverse then
+// next forward 33 + 50 -> 34 + 39 us: the written lines are not left dirty
+// for the next kernel's reads); elsewhere the caches merge the pieces of a
+// line (241 x 241: 24 us, streamed 54 us).
+__device__ __forceinline__ void store_tail8(const PlaneRef& p, int row, int col, int n, bool nt,
                                             const u32x4& w) {
   if (col + 8 <= n) {
-    __builtin_amdgcn_raw_buffer_store_b128(w, p.rs, (row + col) * 2 + p.off, 0, 0);
+    if (nt) __builtin_amdgcn_raw_buffer_store_b128(w, p.rs, (row + col) * 2 + p.off, 0, 2);
+    else __builtin_amdgcn_raw_buffer_store_b128(w, p.rs, (row + col) * 2 + p.off, 0, 0);
   } else {
 #pragma unroll
     for (int e = 0; e < 8; ++e)

@@ -49,6 +49,11 @@ struct R2CArgs {
   // step-B tables at its start and the next item's rows during its last two
   // slices (more registers held per wave)
   int early;
+  // planes of any extents (fno_any.hip)
+  const void* twS;    // [2*Kbp][NF]: cos, -sin of 2 pi t m / Nb, NF = 32 any_nk(Nb)
+  const void* segph;  // fp32 (cos, sin) of 2 pi t NF / Nb, [Kbp]
+  int lw;             // 1 << lw waves share a plane (set by the launcher)
+  int tab_lds;        // step-B tables held in LDS (set by the launcher)
 };
 
 // Inverse of the above: spectrum [planes][Ka][Kb] -> y [planes][Na][Nb],
@@ -82,6 +87,12 @@ struct C2RArgs {
   int lut_sat;      // first code from which f' stays at its +inf value
   const double* bounds;  // ACT_SIGMA: as in R2CArgs
   int bgroup;
+  // planes of any extents (fno_any.hip): [NF][2*Kbp], rows and columns as in
+  // twIc, and the phases, wave and table choices as in R2CArgs
+  const void* twS;
+  const void* segph;
+  int lw;
+  int tab_lds;
 };
 
 // Transforms of 1-D fp16 signals (fno_line.hip): S = planes signals of N
@@ -245,13 +256,9 @@ struct TriArgs {
   int c_ext, Nb;
 };
 hipError_t launch_tucker_tri(const TriArgs& g, hipStream_t s);
-size_t r2c_wide_lds_bytes(int nct, bool pre, int lut_sat);
-size_t c2r_wide_lds_bytes(int nct, int Kap, bool epi, int lut_sat);
-hipError_t launch_r2c_wide(const R2CArgs& a, int nct, int grid, size_t lds, hipStream_t s);
-hipError_t launch_c2r_wide(const C2RArgs& a, int nct, int grid, size_t lds, hipStream_t s);
 hipError_t launch_scale_complex(float* p, int64_t n, float s, hipStream_t st);
 
-// Persistent fp16 fast paths (planes up to 128 x 256); hipErrorNotSupported
+// Persistent fp16 paths of small planes (up to 64 x 64); hipErrorNotSupported
 // when no instantiation matches the shape.
 // nw: waves per work-group, one per 16-row tile of the plane.
 hipError_t launch_r2c_fast(const R2CArgs& a, int nct, int nka, int nw, int grid, size_t lds,
@@ -286,6 +293,12 @@ hipError_t launch_wgrad_slab(const WgradArgs& a, hipStream_t s);
 // Adjoint contraction and weight gradient in one launch (fp16 slab path).
 bool adj_wgrad_slab_supported(const ContractArgs& adj, const WgradArgs& wg);
 hipError_t launch_adj_wgrad_slab(const ContractArgs& adj, const WgradArgs& wg, hipStream_t s);
+
+// fp16 planes of any extents (fno_any.hip); hipErrorNotSupported when the
+// shape is not one of the path's.
+int any_nk(int Nb);  // k-steps of 32 columns in a segment of the last axis
+hipError_t launch_r2c_any(const R2CArgs& a, int nct, int num_cu, hipStream_t s);
+hipError_t launch_c2r_any(const C2RArgs& a, int nct, int num_cu, hipStream_t s);
 
 // Radix-2 wide-plane transforms (fno_wide2.hip): the radix-2 tables in the
 // table fields; hipErrorNotSupported when the shape is not one of the path's.

@@ -100,12 +100,14 @@ __global__ __launch_bounds__(LN_NW * 64, NCT <= 4 ? 2 : 1) void r2c_line_kernel(
   load(signal(0), j + (nbw - 1) * wpp, nxt);
 
   if (PRE) stage_lutn<LN_NW * 64>(lut, a.lut, a.lut_sat);
-  for (int i = tid; i < 2 * KBP * (LN_ROW / 8); i += LN_NW * 64) {
-    const int r = i / (LN_ROW / 8), c = (i % (LN_ROW / 8)) * 8;
-    *reinterpret_cast<u32x4*>(sT + r * LN_LDT + c) =
-        *reinterpret_cast<const u32x4*>(reinterpret_cast<const _Float16*>(a.tw) + r * LN_ROW + c);
-  }
-  for (int i = tid; i < 32 * KBP; i += LN_NW * 64) sR[i] = reinterpret_cast<const f2*>(a.rowph)[i];
+  stage_pieces<LN_NW * 64, 2>(
+      2 * KBP * (LN_ROW / 8), [&](int i) { return reinterpret_cast<const u32x4*>(a.tw) + i; },
+      [&](int i) {
+        return reinterpret_cast<u32x4*>(sT + i / (LN_ROW / 8) * LN_LDT + (i % (LN_ROW / 8)) * 8);
+      });
+  stage_pieces<LN_NW * 64, 1>(
+      16 * KBP, [&](int i) { return reinterpret_cast<const u32x4*>(a.rowph) + i; },
+      [&](int i) { return reinterpret_cast<u32x4*>(sR) + i; });
   // rotation between this wave's blocks, and the phase of its first block
   f2 om[NTB], ph[NTB];
 #pragma unroll
@@ -273,11 +275,12 @@ __global__ __launch_bounds__(LN_NW * 64, 2) void c2r_line_kernel(LineArgs a) {
   u32x4 zn[NKV], xn[2];
   ldz(wave, zn);
   ldx(wave, xn);
-  for (int i = tid; i < LN_CW * NKV * 4; i += LN_NW * 64) {
-    const int r = i / (NKV * 4), c = (i % (NKV * 4)) * 8;
-    *reinterpret_cast<u32x4*>(sT + r * LDT + c) = *reinterpret_cast<const u32x4*>(
-        reinterpret_cast<const _Float16*>(a.tw) + (int64_t)(m0 + r) * NKV * 32 + c);
-  }
+  stage_pieces<LN_NW * 64, NKV>(
+      LN_CW * NKV * 4,
+      [&](int i) { return reinterpret_cast<const u32x4*>(a.tw) + (int64_t)m0 * NKV * 4 + i; },
+      [&](int i) {
+        return reinterpret_cast<u32x4*>(sT + i / (NKV * 4) * LDT + (i % (NKV * 4)) * 8);
+      });
   __syncthreads();
 
 #pragma nounroll
@@ -328,16 +331,14 @@ __global__ __launch_bounds__(LN_NW * 64, 2) void c2r_line_kernel(LineArgs a) {
       if (EPI) {
         u32x4 w = xv[h];
         if (tail && col < a.N && col + 8 > a.N) w = shift_down(w, 8 - tail);
-        const h8 xh = w_as_h8(w);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[h][e] *= preact_grad_f32((float)xh[e], a.act, a.clip);
+        mul_preact_grad8(v[h], w_as_h8(w), a.act, a.clip);
       }
       h8 o;
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = to_h(v[h][e]);
       u32x4 w;
       __builtin_memcpy(&w, &o, 16);
-      store_tail8(py, row, col, a.N, w);
+      store_tail8(py, row, col, a.N, a.N % 64 == 0, w);
     }
   }
 }

@@ -357,6 +357,7 @@ struct DevTables {
   const void *eFr, *eFi, *eIr, *eIi;
   const void *twA2, *cB2, *sB2, *cI2, *sI2, *twI2;  // radix-2 wide-plane tables
   const void *lnF, *lnRow, *lnBlk, *lnI;            // 1-D fp16 signals
+  const void *sgF, *sgI, *sgPh;                     // fp16 planes of any extents
 };
 
 struct Plan {
@@ -599,6 +600,37 @@ void fill_tables(const fno_conv_desc* d, const Geo& g, std::vector<T>& buf,
     buf[olt + code] = (T)f;
     buf[ols + code] = (T)fp;
   }
+  if (nd >= 2 && g.elem == ELEM_F16) {
+    // planes of any extents (fno_any.hip): the twiddles of one segment of the
+    // last axis in both directions, and the fp32 phase of a segment
+    const int nf = 32 * any_nk(g.Nb);
+    size_t sf = alloc((size_t)2 * g.Kbp * nf), si = alloc((size_t)nf * 2 * g.Kbp);
+    size_t sp = alloc((size_t)4 * g.Kbp);
+    for (int t = 0; t < g.Kb; ++t) {
+      double cv, sv;
+      for (int m = 0; m < nf; ++m) {
+        twiddle(t, m, g.Nb, &cv, &sv);
+        buf[sf + (size_t)t * nf + m] = (T)cv;
+        buf[sf + (size_t)(g.Kbp + t) * nf + m] = (T)(-sv);
+      }
+      twiddle(t, nf, g.Nb, &cv, &sv);
+      const float v[2] = {(float)cv, (float)sv};
+      std::memcpy(&buf[sp + 4 * (size_t)t], v, 8);
+    }
+    for (int col = 0; col < 2 * g.Kbp; ++col) {
+      const int ks = col / 32, q = (col % 32) / 8, e = col % 8;
+      const int pair = 2 * ks + e / 4, part = pair / ntb;
+      const int t = 16 * (pair % ntb) + 4 * q + e % 4;
+      if (t >= g.Kb) continue;
+      for (int row = 0; row < nf; ++row) {  // rows in the order of twIc
+        const int tile16 = row / 16, R = row % 16;
+        const int m = 64 * (tile16 / 4) + 16 * (R / 4) + 4 * (tile16 % 4) + R % 4;
+        double cv, sv;
+        twiddle(t, m, g.Nb, &cv, &sv);
+        buf[si + (size_t)row * 2 * g.Kbp + col] = (T)(part == 0 ? cv : -sv);
+      }
+    }
+  }
   (void)o;
   (void)oc;
   (void)os;
@@ -791,25 +823,31 @@ fno_status build_tables(const fno_conv_desc* d, Plan* pl) {
   pl->t.sIc = at(12);
   pl->t.lutAct = at(13);
   pl->t.lutGrad = at(14);
-  if (pl->g.w2) {  // allocated after the lookup tables (2-D plans only)
-    pl->t.twA2 = at(15);
-    pl->t.twI2 = at(16);
-    pl->t.cB2 = at(17);
-    pl->t.sB2 = at(18);
-    pl->t.cI2 = at(19);
-    pl->t.sI2 = at(20);
+  int ix = 15;  // the optional tables follow in the order of fill_tables
+  if (pl->g.nd >= 2 && pl->g.elem == ELEM_F16) {
+    pl->t.sgF = at(ix++);
+    pl->t.sgI = at(ix++);
+    pl->t.sgPh = at(ix++);
+  }
+  if (pl->g.w2) {
+    pl->t.twA2 = at(ix++);
+    pl->t.twI2 = at(ix++);
+    pl->t.cB2 = at(ix++);
+    pl->t.sB2 = at(ix++);
+    pl->t.cI2 = at(ix++);
+    pl->t.sI2 = at(ix++);
   }
   if (pl->g.nd == 1 && pl->g.elem == ELEM_F16) {
-    pl->t.lnF = at(15);
-    pl->t.lnRow = at(16);
-    pl->t.lnBlk = at(17);
-    pl->t.lnI = at(18);
+    pl->t.lnF = at(ix++);
+    pl->t.lnRow = at(ix++);
+    pl->t.lnBlk = at(ix++);
+    pl->t.lnI = at(ix++);
   }
   if (pl->g.nd == 3) {
-    pl->t.eFr = at(15);
-    pl->t.eFi = at(16);
-    pl->t.eIr = at(17);
-    pl->t.eIi = at(18);
+    pl->t.eFr = at(ix++);
+    pl->t.eFi = at(ix++);
+    pl->t.eIr = at(ix++);
+    pl->t.eIi = at(ix++);
   }
   return FNO_OK;
 }
@@ -1132,9 +1170,12 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
       else if (e != hipErrorNotSupported) return hip_fail(e, kname);
     }
   }
-  if (!done && g.elem == ELEM_F16 && a.vec && g.Nb <= 256 && g.Na <= 128 && g.nct <= 8) {
-    const int nka = g.Nb <= 32 ? 1 : g.Nb <= 64 ? 2 : g.Nb <= 128 ? 4 : 8;
-    const int nw = g.Na <= 64 ? 4 : 8;
+  if (!done && g.elem == ELEM_F16 && a.vec && g.Nb <= 64 && g.Na <= 64 && g.nct <= 8) {
+    // small planes, a work-group each: its short start-up counts there (24 x
+    // 24, 256 planes: 6.5 against 8.4 us with tanh in the kernel for any
+    // extents; 72 x 72, 2048 planes: 26.2 against 19.6)
+    const int nka = g.Nb <= 32 ? 1 : 2;
+    const int nw = 4;
     const size_t lds = r2c_fast_lds_bytes(g.nct, nka, nw, g.Kap16, g.Nap_f);
     const int grid = (int)std::min<int64_t>(a.planes, (int64_t)2 * pl->num_cu);
     if (lds <= 80 * 1024) {
@@ -1161,16 +1202,13 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (!done && g.elem == ELEM_F16 && g.Nb % 128 == 0 && g.Na % 256 == 0 && g.Nbp == g.Nb &&
-      (g.nct == 4 || g.nct == 8) && g.Kap16 <= 128 && 128 % g.Kap16 == 0 &&
-      g.Na * (int64_t)g.Nb * 2 < ((int64_t)1 << 30)) {
-    // large planes: persistent eight-wave work-groups, one per compute unit
-    a.lut_sat = pl->t.actSat;
-    const size_t lds = r2c_wide_lds_bytes(g.nct, do_tanh, a.lut_sat);
-    const int grid = (int)std::min<int64_t>(a.planes, (int64_t)pl->num_cu);
-    hipError_t e = timed(kname, s, [&] {
-      return launch_r2c_wide(a, g.nct, grid, lds, s);
-    });
+  if (!done && g.elem == ELEM_F16 && g.nd >= 2) {
+    // every other plane (all but the widest mode counts and the shortest rows)
+    R2CArgs b = a;
+    b.twS = pl->t.sgF;
+    b.segph = pl->t.sgPh;
+    b.lut_sat = pl->t.actSat;
+    hipError_t e = timed(kname, s, [&] { return launch_r2c_any(b, g.nct, pl->num_cu, s); });
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
@@ -1283,10 +1321,12 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
       if (e != hipErrorNotSupported) return hip_fail(e, kname);
     }
   }
-  if (g.elem == ELEM_F16 && a.vec && g.Kb % 4 == 0 && g.Nb <= 256 && g.Na <= 128 && g.nct <= 8 &&
+  if (g.elem == ELEM_F16 && a.vec && g.Kb % 4 == 0 && g.Nb <= 64 && g.Na <= 64 && g.nct <= 8 &&
       g.Kap <= 128) {
-    const int nbt = (g.Nb + 63) / 64;
-    const int nw = g.Na <= 64 ? 4 : 8;
+    // small planes, as in the forward (24 x 24: 6.2 against 9.2 us, 7.1
+    // against 11.0 with tanh'; 40 x 40, 2048 planes: 10.9 against 12.1)
+    const int nbt = 1;
+    const int nw = 4;
     const int nkz = g.Kap / 32;
     const size_t lds = c2r_fast_lds_bytes(g.nct, nw, nbt, nkz);
     const int grid = (int)std::min<int64_t>(a.planes, (int64_t)2 * pl->num_cu);
@@ -1312,13 +1352,11 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (g.elem == ELEM_F16 && g.Nb % 128 == 0 && g.Na % 256 == 0 &&
-      (g.nct == 4 || g.nct == 8) && g.Kap <= 128 && g.Na * (int64_t)g.Nb * 2 < ((int64_t)1 << 30)) {
-    // large planes: persistent eight-wave work-groups, one per compute unit
-    a.lut_sat = pl->t.gradSat;
-    const size_t lds = c2r_wide_lds_bytes(g.nct, g.Kap, x_epi != nullptr, a.lut_sat);
-    const int grid = (int)std::min<int64_t>(a.planes, (int64_t)pl->num_cu);
-    hipError_t e = timed(kname, s, [&] { return launch_c2r_wide(a, g.nct, grid, lds, s); });
+  if (g.elem == ELEM_F16 && g.nd >= 2) {
+    C2RArgs b = a;
+    b.twS = pl->t.sgI;
+    b.segph = pl->t.sgPh;
+    hipError_t e = timed(kname, s, [&] { return launch_c2r_any(b, g.nct, pl->num_cu, s); });
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
