@@ -13,8 +13,12 @@
 //                       g_W[o][i] = sum g_z[o][p] x[i][p] and g_b[o] per work-group
 //   epi_reduce_kernel   the partial sums added in a fixed order
 //
-// Table-free generic kernels cover what the matrix-core kernels do not
-// (points not a multiple of 8, wide channel counts).
+// Channel rows whose length is not a multiple of eight points start at any
+// two-byte address: the pipelined fp16 kernels read and write them with
+// 16-byte accesses at that alignment (RAG; the three calls on 4 x 128 channels of
+// 35 x 35 points took the generic kernels 980 us, these take 69).  Table-free generic kernels cover
+// what the matrix-core kernels do not (wide channel counts, fp32 rows that
+// are not a multiple of eight points).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -77,6 +81,81 @@ template <>
 struct Vec4<float> {
   typedef f4 type;
 };
+
+// Eight fp16 points p .. p + 8 (p < P) of a channel row of P: loaded in one
+// piece, with RAG from P - 8 on where fewer are left (shifted down, with
+// zeros above, when used: row8), and stored (the last partial eight point by
+// point).
+template <bool RAG>
+__device__ __forceinline__ u32x4 load_row8(const _Float16* row, int64_t p, int64_t P) {
+  if (!RAG) return *reinterpret_cast<const u32x4*>(row + p);
+  u32x4 v;
+  __builtin_memcpy(&v, __builtin_assume_aligned(row + (p + 8 <= P ? p : P - 8), 2), 16);
+  return v;
+}
+template <bool RAG>
+__device__ __forceinline__ u32x4 row8(const u32x4& v, int64_t p, int64_t P) {
+  return RAG && p < P && p + 8 > P ? shift_down(v, 8 - (int)(P & 7)) : v;
+}
+template <bool RAG>
+__device__ __forceinline__ void store_row8(_Float16* row, int64_t p, int64_t P, const u32x4& v) {
+  if (!RAG) {
+    *reinterpret_cast<u32x4*>(row + p) = v;
+  } else if (p + 8 <= P) {
+    __builtin_memcpy(__builtin_assume_aligned(row + p, 2), &v, 16);
+  } else {
+    const h8 h = w_as_h8(v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (p + e < P) row[p + e] = h[e];
+  }
+}
+
+// W [rows][cols] (16-byte aligned, at most 128 x 128) into LDS rows of stride
+// ld (zero up to the tile's NR rows and Kp columns), transposed with TR: 16
+// lanes take a row's 16-byte pieces and every load of a thread is in flight
+// before the first is used (element by element, each waited for, a work-group's
+// start took 20 us longer at 128 x 128; 8 x 64 channels of 256 x 256 points,
+// forward 84 -> 75 us).
+template <int NR, bool TR>
+__device__ __forceinline__ void stage_skip(_Float16* WS, int ld, int Kp, const _Float16* w, int N,
+                                           int K) {
+  const int rows = TR ? K : N, cols = TR ? N : K;
+  const int c8 = (threadIdx.x & 15) * 8, r0 = threadIdx.x >> 4;
+  constexpr int RI = TR ? 8 : (NR + 15) / 16;  // row visits of a thread
+  h8 v[RI];
+#pragma unroll
+  for (int i = 0; i < RI; ++i) {
+    const int r = r0 + 16 * i;
+    v[i] = MM<_Float16>::zero();
+    if (r < rows && c8 + 8 <= cols && cols % 8 == 0) {
+      v[i] = *reinterpret_cast<const h8*>(w + r * cols + c8);
+    } else if (r < rows) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (c8 + e < cols) v[i][e] = w[r * cols + c8 + e];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RI; ++i) {
+    const int r = r0 + 16 * i;
+    if (TR) {
+      if (r < Kp) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (c8 + e < NR) WS[(c8 + e) * ld + r] = v[i][e];
+      }
+    } else if (r < NR && c8 < Kp) {
+      *reinterpret_cast<h8*>(WS + r * ld + c8) = v[i];
+    }
+  }
+}
+
+// n halves of LDS (a multiple of 8, 16-byte aligned) to zero, by NT threads.
+template <int NT>
+__device__ __forceinline__ void clear_lds(_Float16* p, int n) {
+  for (int i = threadIdx.x; i < n / 8; i += NT) reinterpret_cast<u32x4*>(p)[i] = u32x4{0u, 0u, 0u, 0u};
+}
 
 struct EpiMixArgs {
   const void* in;    // [B][K][P]
@@ -232,7 +311,7 @@ size_t pipe_lds_bytes(int Kp) {
   return (size_t)((NT * 16 + kPipeP) * ld + 2 * NT * 16 * lda) * 2;
 }
 
-template <int NT, bool FWD>
+template <int NT, bool FWD, bool RAG>
 __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
   using T = _Float16;
   using M = MM<T>;
@@ -262,13 +341,8 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
   const bool gelu = FWD && a.act == FNO_EPI_ACT_GELU;
   const bool resid = FWD && a.residual;
 
-  for (int e = tid; e < NT * 16 * ld; e += 256) {
-    const int n = e / ld, k = e - (e / ld) * ld;
-    T v = (T)0.0f;
-    if (n < a.N && k < a.K) v = FWD ? w[(int64_t)n * a.K + k] : w[(int64_t)k * a.N + n];
-    WS[e] = v;
-  }
-  for (int e = tid; e < kPipeP * ld; e += 256) XT[e] = (T)0.0f;
+  stage_skip<NT * 16, !FWD>(WS, ld, a.Kp, w, a.N, a.K);
+  clear_lds<256>(XT, kPipeP * ld);
   float bv[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
@@ -293,9 +367,9 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
       const int64_t p = p0 + (int64_t)c * 8;
       xr[i][0] = xr[i][1] = u32x4{0u, 0u, 0u, 0u};
       if (v < npv && p < a.P) {
-        const T* src = in + ((b * a.K + 2 * kp) * a.P + p);
-        xr[i][0] = *reinterpret_cast<const u32x4*>(src);
-        if (2 * kp + 1 < a.K) xr[i][1] = *reinterpret_cast<const u32x4*>(src + a.P);
+        const T* src = in + (b * a.K + 2 * kp) * a.P;
+        xr[i][0] = load_row8<RAG>(src, p, a.P);
+        if (2 * kp + 1 < a.K) xr[i][1] = load_row8<RAG>(src + a.P, p, a.P);
       }
     }
 #pragma unroll
@@ -305,9 +379,9 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
       const int64_t p = p0 + (int64_t)c * 8;
       ar1[i] = ar2[i] = u32x4{0u, 0u, 0u, 0u};
       if (v < nav && p < a.P) {
-        const int64_t off = (b * a.N + n) * a.P + p;
-        if (add1) ar1[i] = *reinterpret_cast<const u32x4*>(add1 + off);
-        if (add2) ar2[i] = *reinterpret_cast<const u32x4*>(add2 + off);
+        const int64_t row = (b * a.N + n) * a.P;
+        if (add1) ar1[i] = load_row8<RAG>(add1 + row, p, a.P);
+        if (add2) ar2[i] = load_row8<RAG>(add2 + row, p, a.P);
       }
     }
   };
@@ -324,9 +398,11 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
       const int v = tid + 256 * i;
       if (v < npv) {
         const int kp = v / VPR, c = v - (v / VPR) * VPR;
+        const u32x4 x0 = row8<RAG>(xr[i][0], p0 + c * 8, a.P);
+        const u32x4 x1 = row8<RAG>(xr[i][1], p0 + c * 8, a.P);
         uint16_t lo[8], hi[8];
-        __builtin_memcpy(lo, &xr[i][0], 16);
-        __builtin_memcpy(hi, &xr[i][1], 16);
+        __builtin_memcpy(lo, &x0, 16);
+        __builtin_memcpy(hi, &x1, 16);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const uint32_t pr = (uint32_t)lo[e] | ((uint32_t)hi[e] << 16);
@@ -339,8 +415,9 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
       const int v = tid + 256 * i;
       if (v < nav) {
         const int n = v / VPR, c = v - (v / VPR) * VPR;
-        *reinterpret_cast<u32x4*>(A1 + n * LDA + c * 8) = ar1[i];
-        if (!FWD) *reinterpret_cast<u32x4*>(A2 + n * LDA + c * 8) = ar2[i];
+        *reinterpret_cast<u32x4*>(A1 + n * LDA + c * 8) = row8<RAG>(ar1[i], p0 + c * 8, a.P);
+        if (!FWD)
+          *reinterpret_cast<u32x4*>(A2 + n * LDA + c * 8) = row8<RAG>(ar2[i], p0 + c * 8, a.P);
       }
     }
     __syncthreads();
@@ -387,11 +464,10 @@ __global__ __launch_bounds__(256) void epi_mix_pipe_kernel(EpiMixArgs a) {
       const int n = v / VPR, c = v - (v / VPR) * VPR;
       const int64_t p = p0 + (int64_t)c * 8;
       if (v < nav && p < a.P) {
-        const int64_t off = (b * a.N + n) * a.P + p;
-        *reinterpret_cast<u32x4*>(out + off) = *reinterpret_cast<const u32x4*>(A1 + n * LDA + c * 8);
+        const int64_t row = (b * a.N + n) * a.P;
+        store_row8<RAG>(out + row, p, a.P, *reinterpret_cast<const u32x4*>(A1 + n * LDA + c * 8));
         if (zout)
-          *reinterpret_cast<u32x4*>(zout + off) =
-              *reinterpret_cast<const u32x4*>(A2 + n * LDA + c * 8);
+          store_row8<RAG>(zout + row, p, a.P, *reinterpret_cast<const u32x4*>(A2 + n * LDA + c * 8));
       }
     }
     t = tn;
@@ -569,16 +645,27 @@ __global__ __launch_bounds__(256) void epi_wgrad_kernel(EpiWgradArgs a) {
 // same layout and staged with x in row-major LDS tiles, from which the
 // matrix-core fragments (eight consecutive points per lane) are read.  Wave
 // w owns output-channel tiles w, w + 4 (OTW of them) by every input-channel
-// tile (IT); the next tile's loads are in flight during the products.
+// tile (IT); the next tile's loads are in flight during the products.  Ragged
+// rows have a partial, so a work-group, per 4096 points only: NGRP groups of
+// four waves take its tiles in turn (128 channels of 4 x 35 x 35 points, two
+// work-groups: 203 us with one group).
 constexpr int kWgP = 64;  // grid points per tile of the pipelined weight gradient
 
 template <int OTW, int IT>
-size_t wgrad_pipe_lds_bytes() {
-  return (size_t)(4 * OTW * 16 + IT * 16) * (kWgP + 8) * 2;
+constexpr int wgrad_groups(bool rag) {
+  return !rag ? 1 : OTW * IT <= 8 ? 4 : 2;
 }
 
 template <int OTW, int IT>
-__global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
+size_t wgrad_pipe_lds_bytes(bool rag) {
+  const int n = wgrad_groups<OTW, IT>(rag);
+  const size_t tiles = (size_t)n * (4 * OTW * 16 + IT * 16) * (kWgP + 8) * 2;
+  const size_t sums = (size_t)OTW * IT * 256 * 16 + (size_t)4 * OTW * 16 * (kWgP / 8) * 4;
+  return n > 1 ? std::max(tiles, sums) : tiles;
+}
+
+template <int OTW, int IT, bool RAG, int NGRP>
+__global__ __launch_bounds__(256 * NGRP) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
   using T = _Float16;
   using M = MM<T>;
   using frag = typename M::frag;
@@ -588,16 +675,19 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
   constexpr int XVN = IT * 16 * VPR / 256 > 0 ? IT * 16 * VPR / 256 : 1;
   constexpr int LDA = kWgP + 8;
   extern __shared__ __align__(16) unsigned char smem[];
-  T* GZ = reinterpret_cast<T*>(smem);  // [OROWS][LDA]
-  T* XS = GZ + OROWS * LDA;            // [IT*16][LDA]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255;  // thread of its group
+  T* GZ = reinterpret_cast<T*>(smem) + grp * ((OROWS + IT * 16) * LDA);  // [OROWS][LDA]
+  T* XS = GZ + OROWS * LDA;                                              // [IT*16][LDA]
+  const int lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   const T* x = reinterpret_cast<const T*>(a.x);
   const T* z = reinterpret_cast<const T*>(a.z);
   const T* gout = reinterpret_cast<const T*>(a.gout);
   T* gz = reinterpret_cast<T*>(a.gz);
   const bool gelu = a.act == FNO_EPI_ACT_GELU;
-  const int ngv = a.Cout * VPR, nxv = a.Cin * VPR;
+  // input channels of this work-group: all, or 16 IT of them per grid row
+  const int ic0 = blockIdx.y * IT * 16;
+  const int ngv = a.Cout * VPR, nxv = min(a.Cin - ic0, IT * 16) * VPR;
 
   u32x4 gr[GV], zr[GV], xr[XVN];
   float bs[GV];
@@ -613,9 +703,9 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
       const int64_t p = p0 + (int64_t)c * 8;
       gr[i] = zr[i] = u32x4{0u, 0u, 0u, 0u};
       if (v < ngv && p < a.P) {
-        const int64_t off = (b * a.Cout + o) * a.P + p;
-        gr[i] = *reinterpret_cast<const u32x4*>(gout + off);
-        if (gelu) zr[i] = *reinterpret_cast<const u32x4*>(z + off);
+        const int64_t row = (b * a.Cout + o) * a.P;
+        gr[i] = load_row8<RAG>(gout + row, p, a.P);
+        if (gelu) zr[i] = load_row8<RAG>(z + row, p, a.P);
       }
     }
 #pragma unroll
@@ -624,7 +714,7 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
       const int ic = v / VPR, c = v - (v / VPR) * VPR;
       const int64_t p = p0 + (int64_t)c * 8;
       xr[i] = u32x4{0u, 0u, 0u, 0u};
-      if (v < nxv && p < a.P) xr[i] = *reinterpret_cast<const u32x4*>(x + (b * a.Cin + ic) * a.P + p);
+      if (v < nxv && p < a.P) xr[i] = load_row8<RAG>(x + (b * a.Cin + ic0 + ic) * a.P, p, a.P);
     }
   };
 
@@ -634,26 +724,34 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
 #pragma unroll
     for (int it = 0; it < IT; ++it) acc[u][it] = f4zero();
   // rows beyond the channel counts stay zero in LDS
-  for (int e = tid; e < (OROWS + IT * 16) * LDA; e += 256) GZ[e] = (T)0.0f;
+  clear_lds<256 * NGRP>(reinterpret_cast<T*>(smem), NGRP * (OROWS + IT * 16) * LDA);
 
-  int64_t t = blockIdx.x;
+  // the groups take tiles in turn (the same number of barriers each)
+  const int64_t step = (int64_t)gridDim.x * NGRP;
+  int64_t t = (int64_t)blockIdx.x * NGRP + grp;
   if (t < a.tiles) load(t);
-  while (t < a.tiles) {
+  for (int64_t first = (int64_t)blockIdx.x * NGRP; first < a.tiles; first += step) {
+    const bool on = NGRP == 1 || t < a.tiles;
     const int64_t b = t / a.ptiles;
     const int64_t p0 = (t - b * a.ptiles) * kWgP;
     __syncthreads();  // the previous tile's fragments are read
+    if (on) {
 #pragma unroll
     for (int i = 0; i < GV; ++i) {
       const int v = tid + 256 * i;
       if (v < ngv) {
         const int o = v / VPR, c = v - (v / VPR) * VPR;
-        h8 gv = w_as_h8(gr[i]);
         const int64_t p = p0 + (int64_t)c * 8;
+        h8 gv = w_as_h8(row8<RAG>(gr[i], p, a.P));
         if (gelu) {
-          const h8 zv = w_as_h8(zr[i]);
+          const h8 zv = w_as_h8(row8<RAG>(zr[i], p, a.P));
 #pragma unroll
           for (int e = 0; e < 8; ++e) gv[e] = (T)((float)gv[e] * gelu_grad_f((float)zv[e]));
-          if (p < a.P) *reinterpret_cast<h8*>(gz + (b * a.Cout + o) * a.P + p) = gv;
+          if (p < a.P) {
+            u32x4 w;
+            __builtin_memcpy(&w, &gv, 16);
+            store_row8<RAG>(gz + (b * a.Cout + o) * a.P, p, a.P, w);
+          }
         }
         float sum = 0.0f;
 #pragma unroll
@@ -667,14 +765,16 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
       const int v = tid + 256 * i;
       if (v < nxv) {
         const int ic = v / VPR, c = v - (v / VPR) * VPR;
-        *reinterpret_cast<u32x4*>(XS + ic * LDA + c * 8) = xr[i];
+        *reinterpret_cast<u32x4*>(XS + ic * LDA + c * 8) = row8<RAG>(xr[i], p0 + c * 8, a.P);
       }
     }
+    }
     __syncthreads();
-    const int64_t tn = t + gridDim.x;
+    const int64_t tn = t + step;
     if (tn < a.tiles) load(tn);  // in flight during the products
 #pragma unroll
     for (int k0 = 0; k0 < kWgP; k0 += 32) {
+      if (!on) break;
       frag af[OTW], bf[IT];
 #pragma unroll
       for (int u = 0; u < OTW; ++u)
@@ -688,6 +788,39 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
     }
     t = tn;
   }
+  // bias sums: the eight lanes of a row segment hold parts of one channel
+#pragma unroll
+  for (int i = 0; i < GV; ++i) {
+    bs[i] += __shfl_xor(bs[i], 1);
+    bs[i] += __shfl_xor(bs[i], 2);
+    bs[i] += __shfl_xor(bs[i], 4);
+  }
+  // the groups' sums added in order: group q to group 0 through LDS
+  if constexpr (NGRP > 1) {
+    f4* ra = reinterpret_cast<f4*>(smem);  // [OTW * IT][256]
+    float* rb = reinterpret_cast<float*>(ra + OTW * IT * 256);  // [GV][256]
+    for (int q = 1; q < NGRP; ++q) {
+      __syncthreads();
+      if (grp == q) {
+#pragma unroll
+        for (int u = 0; u < OTW; ++u)
+#pragma unroll
+          for (int it = 0; it < IT; ++it) ra[(u * IT + it) * 256 + tid] = acc[u][it];
+#pragma unroll
+        for (int i = 0; i < GV; ++i) rb[i * 256 + tid] = bs[i];
+      }
+      __syncthreads();
+      if (grp == 0) {
+#pragma unroll
+        for (int u = 0; u < OTW; ++u)
+#pragma unroll
+          for (int it = 0; it < IT; ++it) acc[u][it] += ra[(u * IT + it) * 256 + tid];
+#pragma unroll
+        for (int i = 0; i < GV; ++i) bs[i] += rb[i * 256 + tid];
+      }
+    }
+    if (grp != 0) return;
+  }
   // this work-group's partial sums: each (o, i) element belongs to one lane
   const int64_t E = (int64_t)a.Cout * a.Cin + a.Cout;
   float* part = a.part + (int64_t)blockIdx.x * E;
@@ -697,18 +830,28 @@ __global__ __launch_bounds__(256) void epi_wgrad_pipe_kernel(EpiWgradArgs a) {
     for (int it = 0; it < IT; ++it)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int o = (wave + 4 * u) * 16 + 4 * g + q, ic = it * 16 + r16;
+        const int o = (wave + 4 * u) * 16 + 4 * g + q, ic = ic0 + it * 16 + r16;
         if (o < a.Cout && ic < a.Cin) part[(int64_t)o * a.Cin + ic] = acc[u][it][q];
       }
-  // bias sums: the eight lanes of a row segment hold parts of one channel
 #pragma unroll
   for (int i = 0; i < GV; ++i) {
-    float v = bs[i];
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
     const int vv = tid + 256 * i;
-    if ((vv & (VPR - 1)) == 0 && vv < ngv) part[(int64_t)a.Cout * a.Cin + vv / VPR] = v;
+    if (ic0 == 0 && (vv & (VPR - 1)) == 0 && vv < ngv) part[(int64_t)a.Cout * a.Cin + vv / VPR] = bs[i];
+  }
+}
+
+// g_z = g_out act'(z) of n fp16 elements, eight per thread.
+__global__ __launch_bounds__(256) void epi_gz_kernel(const _Float16* gout, const _Float16* z,
+                                                     _Float16* gz, int64_t n) {
+  const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (q + 8 <= n) {
+    h8 v = *reinterpret_cast<const h8*>(gout + q);
+    const h8 zv = *reinterpret_cast<const h8*>(z + q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (_Float16)((float)v[e] * gelu_grad_f((float)zv[e]));
+    *reinterpret_cast<h8*>(gz + q) = v;
+  } else {
+    for (int64_t i = q; i < n; ++i) gz[i] = (_Float16)((float)gout[i] * gelu_grad_f((float)z[i]));
   }
 }
 
@@ -833,11 +976,12 @@ bool wgrad_fast(const EpiGeo& g, int* it, int* og, int* wpr) {
   return true;
 }
 
-// The pipelined fp16 weight gradient: points a multiple of 8, at most 128
-// channels each way.
-bool wgrad_pipe(const EpiGeo& g) {
-  return g.es == 2 && g.P % 8 == 0 && g.Cin <= 128 && g.Cout <= 128;
+// The pipelined fp16 kernels: at least one 16-byte piece of points per
+// channel row, at most 128 channels each way.
+bool mix_pipe(const EpiGeo& g, int K, int N) {
+  return g.es == 2 && g.P >= 8 && K <= 128 && N <= 128;
 }
+bool wgrad_pipe(const EpiGeo& g) { return mix_pipe(g, g.Cin, g.Cout); }
 
 // Partial sums of the weight gradient: count and bytes.
 int wgrad_partials(const EpiGeo& g, int64_t* tiles, int64_t* ptiles) {
@@ -847,6 +991,8 @@ int wgrad_partials(const EpiGeo& g, int64_t* tiles, int64_t* ptiles) {
   if (wgrad_pipe(g)) {
     *ptiles = cdiv(g.P, kWgP);
     *tiles = g.B * *ptiles;
+    // ragged rows keep the generic kernels' workspace: a partial per 4096 points
+    if (g.P % 8 != 0) cap = std::min(cap, cdiv(g.B * g.P, 4096));
   } else if (wgrad_fast(g, &it, &og, &wpr)) {
     const int ranges = 4 / wpr;
     *ptiles = cdiv(g.P, (int64_t)kWaveP * ranges);
@@ -882,7 +1028,7 @@ struct EpiMixLaunch {
   EpiMixArgs a;
   int es;
   hipStream_t s;
-  bool fast;
+  bool pipe, fast;
 };
 
 template <typename T, int NT, bool FWD>
@@ -903,9 +1049,10 @@ hipError_t launch_mix_fast(const EpiMixArgs& a, int grid, size_t lds, hipStream_
 
 template <int NT, bool FWD>
 hipError_t launch_pipe_nt(const EpiMixArgs& a, int grid, size_t lds, hipStream_t s) {
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&epi_mix_pipe_kernel<NT, FWD>), lds);
+  auto k = a.P % 8 ? epi_mix_pipe_kernel<NT, FWD, true> : epi_mix_pipe_kernel<NT, FWD, false>;
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(k), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((epi_mix_pipe_kernel<NT, FWD>), dim3(grid), dim3(256), lds, s, a);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, s, a);
   return hipSuccess;
 }
 
@@ -923,7 +1070,7 @@ hipError_t launch_pipe(const EpiMixArgs& a, int grid, hipStream_t s) {
 template <typename T>
 hipError_t launch_mix_t(EpiMixLaunch* L) {
   EpiMixArgs& a = L->a;
-  if (L->fast && sizeof(T) == 2 && a.ntt <= 8 && a.K <= 128) {
+  if (L->pipe) {
     const int64_t tiles = a.B * cdiv(a.P, kPipeP);
     a.ptiles = cdiv(a.P, kPipeP);
     a.tiles = tiles;
@@ -973,6 +1120,7 @@ fno_status run_mix(const EpiGeo& g, const char* name, const void* in, int K, con
   a.tiles = g.B * a.ptiles;
   L.es = g.es;
   L.s = s;
+  L.pipe = mix_pipe(g, K, N);
   L.fast = mix_fast(g, K, N);
   const hipError_t e = timed_launch(name, s, launch_mix, &L);
   return e == hipSuccess ? FNO_OK : report_hip_error(e, name);
@@ -993,9 +1141,38 @@ hipError_t launch_wgrad_t(EpiWgradLaunch* L) {
   const int64_t E = (int64_t)a.Cout * a.Cin + a.Cout;
   if (L->pipe) {
     const int cit = (int)cdiv(a.Cin, 16);
-    const int itp = cit <= 1 ? 1 : cit <= 2 ? 2 : cit <= 4 ? 4 : 8;
+    int itp = cit <= 1 ? 1 : cit <= 2 ? 2 : cit <= 4 ? 4 : 8;
     const int otw = a.Cout <= 64 ? 1 : 2;
-#define FNO_WGP(OTWV, ITV)                                                                     if (otw == OTWV && itp == ITV) {                                                               const size_t lds = wgrad_pipe_lds_bytes<OTWV, ITV>();                                        hipError_t e = allow_lds(reinterpret_cast<const void*>(&epi_wgrad_pipe_kernel<OTWV, ITV>), lds);     if (e != hipSuccess) return e;                                                               hipLaunchKernelGGL((epi_wgrad_pipe_kernel<OTWV, ITV>), dim3(L->G), dim3(256), lds, L->s, a);   }
+    int rows = 1;
+    if (a.P % 8 != 0 && L->G * cit <= 256) {
+      // few partials (ragged rows): g_z in a pass of its own over all points,
+      // then 16 input channels per work-group (4 x 35 x 35 points, 128
+      // channels: 139 us with everything in the partials' two work-groups)
+      if (a.act == FNO_EPI_ACT_GELU) {
+        const int64_t n = a.B * a.Cout * a.P;
+        hipLaunchKernelGGL(epi_gz_kernel, dim3((unsigned)cdiv(n, 2048)), dim3(256), 0, L->s,
+                           reinterpret_cast<const _Float16*>(a.gout),
+                           reinterpret_cast<const _Float16*>(a.z),
+                           reinterpret_cast<_Float16*>(a.gz), n);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        a.gout = a.gz;
+        a.act = FNO_EPI_ACT_NONE;
+      }
+      itp = 1;
+      rows = cit;
+    }
+#define FNO_WGP(OTWV, ITV)                                                                    \
+  if (otw == OTWV && itp == ITV) {                                                            \
+    const bool rag = a.P % 8 != 0;                                                            \
+    constexpr int n = wgrad_groups<OTWV, ITV>(true);                                          \
+    const size_t lds = wgrad_pipe_lds_bytes<OTWV, ITV>(rag);                                  \
+    auto k = rag ? epi_wgrad_pipe_kernel<OTWV, ITV, true, n>                                  \
+                 : epi_wgrad_pipe_kernel<OTWV, ITV, false, 1>;                                \
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(k), lds);                          \
+    if (e != hipSuccess) return e;                                                            \
+    hipLaunchKernelGGL(k, dim3(L->G, rows), dim3(rag ? 256 * n : 256), lds, L->s, a);             \
+  }
     FNO_WGP(1, 1) else FNO_WGP(1, 2) else FNO_WGP(1, 4) else FNO_WGP(1, 8)
     else FNO_WGP(2, 1) else FNO_WGP(2, 2) else FNO_WGP(2, 4) else FNO_WGP(2, 8)
     else return hipErrorInvalidValue;
