@@ -37,6 +37,9 @@
  *     calls into a HIP graph.
  *   - All argument checks run on the host before anything is enqueued; a
  *     rejected call enqueues nothing.  Calls are asynchronous on `stream`.
+ *   - A transform's output (y, gx) may hold intermediate sums of the call
+ *     before its results are written, where its memory overlaps none of the
+ *     call's inputs.
  *   - The plan cache is mutex-guarded; concurrent calls on different streams
  *     are safe as long as their workspaces and outputs do not overlap.
  *   - Calls run on the current device, whose stream `stream` must be.  With

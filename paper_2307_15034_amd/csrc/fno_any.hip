@@ -59,7 +59,7 @@ size_t any_c2r_lds(int nct, int nk, int lw, int kap, bool epi) {
 // ---------------------------------------------------------------------------
 // Forward: plane [Na][Nb] -> spectrum [Ka][Kb].
 // ---------------------------------------------------------------------------
-template <int NCT, int NK, bool PRE>
+template <int NCT, int NK, bool PRE, bool SHARE>
 __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R2CArgs a) {
   constexpr int KBP = NCT * 8, NTB = NCT / 2, NF = NK * 32, LDT = NF + 8;
   extern __shared__ __align__(16) unsigned char smem[];  // the table at LDS byte 0
@@ -77,10 +77,21 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
 
   const int nblk = (a.Na + 31) / 32, nseg = (a.Nb + NF - 1) / NF;
   const int nch = (nblk + wpp - 1) >> a.lw;  // chunks of a plane (1 unless wpp is 8)
+  // SHARE: the chunks of a plane are shared by a.parts work-groups, which have
+  // one plane each (too few planes): this one's chunks
+  const int parts = SHARE ? a.parts : 1;
+  const int cpp = (nch + parts - 1) / parts;
+  const int part = SHARE ? (int)(blockIdx.x % parts) : 0;
+  const int ch0 = part * cpp, ch1 = SHARE ? min(nch, ch0 + cpp) : nch;
   const int tail = a.Nb & 7;
   const int64_t plane_bytes = (int64_t)a.Na * a.Nb * 2;
-  const int64_t trips = (a.planes + (int64_t)gridDim.x * ngrp - 1) / ((int64_t)gridDim.x * ngrp);
-  auto plane_of = [&](int64_t t) { return ((int64_t)blockIdx.x + t * gridDim.x) * ngrp + grp; };
+  const int64_t trips =
+      SHARE ? 1
+            : (a.planes + (int64_t)gridDim.x * ngrp - 1) / ((int64_t)gridDim.x * ngrp);
+  auto plane_of = [&](int64_t t) {
+    return SHARE ? (int64_t)(blockIdx.x / parts)
+                 : ((int64_t)blockIdx.x + t * gridDim.x) * ngrp + grp;
+  };
 
   // k-step k of segment sg of a row block: lane holds rows 32 b + 16 u + r16,
   // columns NF sg + 32 k + 8 g .. + 8
@@ -102,7 +113,7 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
   };
   u32x4 nxt[2][NK];
   {
-    const Rows r = rows_of(plane_of(0), j);
+    const Rows r = rows_of(plane_of(0), ch0 * wpp + j);
 #pragma unroll
     for (int k = 0; k < NK; ++k) load(r, nseg - 1, k, nxt);
   }
@@ -138,7 +149,7 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
     const int64_t p = plane_of(t);
     const int64_t pn = t + 1 < trips ? plane_of(t + 1) : a.planes;
 #pragma nounroll
-    for (int ch = 0; ch < nch; ++ch) {
+    for (int ch = ch0; ch < ch1; ++ch) {
       const int b = ch * wpp + j;
       f4 acc[2][NCT];
 #pragma unroll
@@ -159,7 +170,7 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
         const int ktail = tail && sg == nseg - 1 ? (a.Nb - sg * NF) / 32 : -1;
         // the next segment (of the next chunk or plane at the end), requested
         // k-step by k-step as this one's registers are used up
-        const bool same = sg > 0, chn = ch + 1 < nch;
+        const bool same = sg > 0, chn = ch + 1 < ch1;
         const Rows rn = rows_of(same || chn ? p : pn, same ? b : (chn ? b + wpp : j));
         const int sn = same ? sg - 1 : nseg - 1;
 #pragma unroll
@@ -203,7 +214,7 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
 
       const int nb = min(wpp, nblk - ch * wpp);
       for (int ta = j % q; ta < nta; ta += q) {
-        if (ch == 0) {
+        if (ch == ch0) {
 #pragma unroll
           for (int jj = 0; jj < NTB; ++jj) zr[jj] = zi[jj] = f4zero();
         }
@@ -233,7 +244,19 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
           const _Float16* sb = reinterpret_cast<const _Float16*>(a.sBc) + eo;
           for (int kb = 0; kb < nb; ++kb) products(kb, MH::ld(cb + kb * 32), MH::ld(sb + kb * 32));
         }
-        if (ch == nch - 1 && p < a.planes) {
+        if (SHARE && ch == ch1 - 1) {
+          // this part's sums, unscaled in fp32, to be added in order
+          f2* sum = reinterpret_cast<f2*>(a.part) + (int64_t)blockIdx.x * a.Ka * a.Kb;
+#pragma unroll
+          for (int jj = 0; jj < NTB; ++jj) {
+            const int t_b = (tb0 + jj * tbs) * 16 + r16;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int t_a = ta * 16 + 4 * g + i;
+              if (t_a < a.Ka && t_b < a.Kb) sum[t_a * a.Kb + t_b] = f2{zr[jj][i], zi[jj][i]};
+            }
+          }
+        } else if (ch == ch1 - 1 && p < a.planes) {
           _Float16* out = reinterpret_cast<_Float16*>(a.out) + p * (int64_t)a.Ka * a.Kb * 2;
 #pragma unroll
           for (int jj = 0; jj < NTB; ++jj) {
@@ -264,7 +287,7 @@ __global__ __launch_bounds__(AN_NW * 64, NCT <= 4 ? 4 : 2) void r2c_any_kernel(R
 // lanes store, and read x of, 128 consecutive bytes of a row.  f' is evaluated
 // in fp32.
 // ---------------------------------------------------------------------------
-template <int NCT, int NK, bool EPI>
+template <int NCT, int NK, bool EPI, bool SHARE>
 __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
   constexpr int KBP = NCT * 8, NTB = NCT / 2, NF = NK * 32, NKV = NCT / 2;
   constexpr int LDT = 2 * KBP + 8, NU = NF / 64;
@@ -290,8 +313,19 @@ __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
   const int64_t plane_bytes = (int64_t)a.Na * a.Nb * 2;
   const int spec = a.Ka * a.Kb;  // complex values of a spectrum plane
   const int gt = tid - grp * wpp * 64, gn = wpp * 64;  // thread in the group that shares a plane
-  const int64_t trips = (a.planes + (int64_t)gridDim.x * ngrp - 1) / ((int64_t)gridDim.x * ngrp);
-  auto plane_of = [&](int64_t t) { return ((int64_t)blockIdx.x + t * gridDim.x) * ngrp + grp; };
+  // SHARE: the row blocks of a plane are shared by a.parts work-groups, as in
+  // the forward: this one's blocks b0 + j + wpp i below b1
+  const int parts = SHARE ? a.parts : 1;
+  const int bpp = ((nblk + wpp - 1) / wpp + parts - 1) / parts * wpp;
+  const int b0 = SHARE ? (int)(blockIdx.x % parts) * bpp : 0;
+  const int b1 = SHARE ? min(nblk, b0 + bpp) : nblk;
+  const int64_t trips =
+      SHARE ? 1
+            : (a.planes + (int64_t)gridDim.x * ngrp - 1) / ((int64_t)gridDim.x * ngrp);
+  auto plane_of = [&](int64_t t) {
+    return SHARE ? (int64_t)(blockIdx.x / parts)
+                 : ((int64_t)blockIdx.x + t * gridDim.x) * ngrp + grp;
+  };
 
   // spectrum of plane p, transposed into ZT[kb | KBP + kb][ka]; the padding
   // stays zero (every plane writes the same positions)
@@ -352,7 +386,7 @@ __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
 
   u32x4 zn[ZQ], xn[2][2];
   ldz(plane_of(0), zn);
-  ldx(plane_of(0), j, 0, xn);
+  ldx(plane_of(0), b0 + j, 0, xn);
   stage_pieces<AN_NW * 64, 2>(
       NF * (2 * KBP / 8), [&](int i) { return reinterpret_cast<const u32x4*>(a.twS) + i; },
       [&](int i) {
@@ -379,7 +413,7 @@ __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
     const PlaneRef py = plane_ref_at(a.out, p < a.planes ? p * plane_bytes : 0,
                                      p < a.planes ? plane_bytes : 0);
 #pragma nounroll
-    for (int b = j; b < nblk; b += wpp) {
+    for (int b = b0 + j; b < b1; b += wpp) {
       // ---- step B' ----
       f4 vr[2][NTB], vi[2][NTB];
 #pragma unroll
@@ -466,8 +500,8 @@ __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
             for (int u = 0; u < 2; ++u)
 #pragma unroll
               for (int h = 0; h < 2; ++h) xv[u][h] = xn[u][h];
-            const bool same = c + 1 < nun, blk = b + wpp < nblk;
-            ldx(same || blk ? p : pn, same ? b : (blk ? b + wpp : j), same ? c + 1 : 0, xn);
+            const bool same = c + 1 < nun, blk = b + wpp < b1;
+            ldx(same || blk ? p : pn, same ? b : (blk ? b + wpp : b0 + j), same ? c + 1 : 0, xn);
           }
           f4 acc[2][4];
 #pragma unroll
@@ -538,6 +572,28 @@ __global__ __launch_bounds__(AN_NW * 64, 2) void c2r_any_kernel(C2RArgs a) {
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+// Spectrum of plane p from the sums of its parts, [planes][parts][K] in fp32:
+// added in order, scaled and rounded once.
+__global__ __launch_bounds__(256) void part_sum_kernel(const f2* part, h2* out, int parts,
+                                                       int64_t K, int64_t n, float scale) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int64_t p = i / K, k = i - p * K;
+  const f2* src = part + p * parts * K + k;
+  f2 v = src[0];
+  for (int s = 1; s < parts; ++s) v += src[s * K];
+  out[i] = h2{to_h(v[0] * scale), to_h(v[1] * scale)};
+}
+
+hipError_t launch_part_sum(const void* part, void* out, int parts, int64_t planes, int64_t K,
+                           float scale, hipStream_t s) {
+  const int64_t n = planes * K;
+  hipLaunchKernelGGL(part_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<const f2*>(part), reinterpret_cast<h2*>(out), parts, K, n,
+                     scale);
+  return hipGetLastError();
+}
+
 // columns of a segment, in k-steps: 128 unless the row is that short
 int any_nk(int Nb) { return Nb <= 64 ? 2 : 4; }
 
@@ -565,10 +621,15 @@ hipError_t launch_r2c_any(const R2CArgs& a_in, int nct, int num_cu, hipStream_t 
   if (a.tab_lds) lds += tab;
   if (lds > 160 * 1024) return hipErrorNotSupported;
   const int64_t ngrp = AN_NW >> a.lw;
-  const int grid = (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp, (int64_t)per_cu * num_cu);
+  const int grid = a.parts > 1 ? (int)a.planes * a.parts
+                               : (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp,
+                                                        (int64_t)per_cu * num_cu);
 #define FNO_ANY_F(N, K)                                                                   \
   if (nct == N && nk == K) {                                                              \
-    auto k = pre ? r2c_any_kernel<N, K, true> : r2c_any_kernel<N, K, false>;              \
+    auto k = a.parts > 1 ? (pre ? r2c_any_kernel<N, K, true, true>                        \
+                                : r2c_any_kernel<N, K, false, true>)                      \
+                         : (pre ? r2c_any_kernel<N, K, true, false>                       \
+                                : r2c_any_kernel<N, K, false, false>);                    \
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                  \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     if (e != hipSuccess) return e;                                                        \
@@ -594,10 +655,15 @@ hipError_t launch_c2r_any(const C2RArgs& a_in, int nct, int num_cu, hipStream_t 
   if (a.tab_lds) lds += tab;
   if (lds > 160 * 1024) return hipErrorNotSupported;
   const int64_t ngrp = AN_NW >> a.lw;
-  const int grid = (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp, (int64_t)per_cu * num_cu);
+  const int grid = a.parts > 1 ? (int)a.planes * a.parts
+                               : (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp,
+                                                        (int64_t)per_cu * num_cu);
 #define FNO_ANY_I(N, K)                                                                   \
   if (nct == N && nk == K) {                                                              \
-    auto k = a.epilogue ? c2r_any_kernel<N, K, true> : c2r_any_kernel<N, K, false>;       \
+    auto k = a.parts > 1 ? (a.epilogue ? c2r_any_kernel<N, K, true, true>                 \
+                                       : c2r_any_kernel<N, K, false, true>)               \
+                         : (a.epilogue ? c2r_any_kernel<N, K, true, false>                \
+                                       : c2r_any_kernel<N, K, false, false>);             \
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                  \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     if (e != hipSuccess) return e;                                                        \

@@ -54,6 +54,11 @@ struct R2CArgs {
   const void* segph;  // fp32 (cos, sin) of 2 pi t NF / Nb, [Kbp]
   int lw;             // 1 << lw waves share a plane (set by the launcher)
   int tab_lds;        // step-B tables held in LDS (set by the launcher)
+  // fno_wide2.hip and fno_any.hip: work-groups that share a plane's rows (1,
+  // or more where planes are few), and then the fp32 sums of every part,
+  // [planes][parts][Ka][Kb], which launch_part_sum adds
+  int parts;
+  void* part;
 };
 
 // Inverse of the above: spectrum [planes][Ka][Kb] -> y [planes][Na][Nb],
@@ -93,6 +98,7 @@ struct C2RArgs {
   const void* segph;
   int lw;
   int tab_lds;
+  int parts;          // work-groups that share a plane's rows, as in R2CArgs
 };
 
 // Transforms of 1-D fp16 signals (fno_line.hip): S = planes signals of N
@@ -296,6 +302,8 @@ hipError_t launch_adj_wgrad_slab(const ContractArgs& adj, const WgradArgs& wg, h
 
 // fp16 planes of any extents (fno_any.hip); hipErrorNotSupported when the
 // shape is not one of the path's.
+hipError_t launch_part_sum(const void* part, void* out, int parts, int64_t planes, int64_t K,
+                           float scale, hipStream_t s);
 int any_nk(int Nb);  // k-steps of 32 columns in a segment of the last axis
 hipError_t launch_r2c_any(const R2CArgs& a, int nct, int num_cu, hipStream_t s);
 hipError_t launch_c2r_any(const C2RArgs& a, int nct, int num_cu, hipStream_t s);

@@ -1085,10 +1085,66 @@ fno_status run_sigma_stats(const Plan* pl, const void* x, double* bounds, hipStr
   return FNO_OK;
 }
 
+// Work-groups that share a plane's rows in the 2-D fp16 transforms of large
+// planes, where there are fewer planes than half the compute units (64 planes
+// of 1024 x 1024: forward with tanh 96 us with one work-group per plane, 49
+// with four and the sum of their parts; inverse 96 and 40 us).  The
+// radix-2 kernels split a plane's chunks of 256 rows evenly, the others any way.
+int plane_parts(const Plan* pl, int64_t planes, bool even) {
+  const Geo& g = pl->g;
+  if (g.nd != 2 || g.elem != ELEM_F16 || planes * 2 > pl->num_cu) return 1;
+  const int nch = (g.Na + 255) / 256;
+  int parts = (int)std::min<int64_t>(nch, pl->num_cu / planes);
+  while (even && nch % parts) --parts;
+  if (!even) parts = (nch + (nch + parts - 1) / parts - 1) / ((nch + parts - 1) / parts);
+  return parts;
+}
+
+// Memory that a call may use before it writes its output there: the output
+// itself, where it overlaps nothing that the call reads or writes earlier
+// (inputs may lie in the output's memory: the last transform alone writes it).
+struct Spare {
+  void* p = nullptr;
+  size_t bytes = 0;
+};
+
+Spare spare_output(const fno_conv_desc* d, const Plan* pl, void* out, int64_t c_out, const void* in,
+                   int64_t c_in, const void* in2, int64_t c_in2, const fno_weights* w,
+                   const void* spec, const void* spec2) {
+  const Geo& g = pl->g;
+  if (plane_parts(pl, g.B * c_in, false) == 1) return Spare{};
+  const uintptr_t a = (uintptr_t)out;
+  const size_t bytes = (size_t)(g.B * c_out * g.N * g.es);
+  auto apart = [&](const void* p, int64_t n) {
+    const uintptr_t b = (uintptr_t)p;
+    return !p || a >= b + (size_t)(n * g.es) || b >= a + bytes;
+  };
+  const int64_t sp = 2 * g.B * g.K * std::max(g.Cin, g.Cout);
+  bool ok = apart(in, g.B * c_in * g.N) && apart(in2, g.B * c_in2 * g.N) && apart(spec, sp) &&
+            apart(spec2, sp);
+  if (d->weight_kind == FNO_WEIGHT_DENSE) {
+    ok = ok && apart(w->dense, 2 * g.Cin * g.Cout * g.K);
+  } else {
+    const bool cp = d->weight_kind == FNO_WEIGHT_CP;
+    const int64_t r0 = d->rank[0], r1 = cp ? r0 : d->rank[1];
+    int64_t core = cp ? r0 : r0 * r1;
+    for (int j = 0; j < g.nd; ++j) {
+      const int64_t r = cp ? r0 : d->rank[2 + j];
+      if (!cp) core *= r;
+      ok = ok && apart(w->u_mode[j], 2 * kextent(d, j) * r);
+    }
+    ok = ok && apart(w->core, 2 * core) && apart(w->u_in, 2 * g.Cin * r0) &&
+         apart(w->u_out, 2 * g.Cout * r1);
+  }
+  return ok ? Spare{out, bytes} : Spare{};
+}
+
 // bounds: the clip bounds of the statistics-based pre-activation (read when
-// it is applied to the input).
+// it is applied to the input).  spare: memory for the parts' sums of planes
+// shared by several work-groups (none: planes are not shared).
 fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int64_t C,
-                   int pre, int scale_mode, hipStream_t s, const double* bounds = nullptr) {
+                   int pre, int scale_mode, hipStream_t s, const double* bounds = nullptr,
+                   Spare spare = Spare{}) {
   const Geo& g = pl->g;
   R2CArgs a{};
   a.zeros = pl->t.zeros;
@@ -1136,6 +1192,19 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
   a.sBc = pl->t.sBc;
   a.NaC = g.NaC;
   a.lut = pl->t.lutAct;
+  a.parts = 1;
+  auto share = [&](bool even) {  // planes shared by several work-groups
+    a.parts = 1;
+    const int n = plane_parts(pl, a.planes, even);
+    if (n > 1 && (size_t)(a.planes * n * g.K * 8) <= spare.bytes) {
+      a.parts = n;
+      a.part = spare.p;
+    }
+  };
+  auto add_parts = [&]() {
+    if (a.parts == 1) return hipSuccess;
+    return launch_part_sum(a.part, a.out, a.parts, a.planes, g.K, a.scaleB, s);
+  };
   if (a.planes > 0x7fffffff || (g.nd == 3 && g.B * C > 65535)) return FNO_ERR_UNSUPPORTED;
   bool done = sigma;
   if (!done && g.elem == ELEM_F16 && g.nd == 1) {
@@ -1189,6 +1258,7 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
   if (!done && g.w2) {
     // large planes, one radix-2 stage per axis: persistent eight-wave
     // work-groups, one per compute unit
+    share(true);
     R2CArgs b = a;
     b.twA = pl->t.twA2;
     b.cB = pl->t.cB2;
@@ -1197,18 +1267,25 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     b.lut_sat = pl->t.actSat;
     b.early = pl->r2c_early ? 1 : 0;
     const size_t lds = r2c_wide2_lds_bytes(g.w2_nctc, do_tanh, b.lut_sat);
-    const int grid = (int)std::min<int64_t>(a.planes, (int64_t)pl->num_cu);
-    hipError_t e = timed(kname, s, [&] { return launch_r2c_wide2(b, g.w2_nctc, grid, lds, s); });
+    const int grid = (int)std::min<int64_t>(a.planes * a.parts, (int64_t)pl->num_cu);
+    hipError_t e = timed(kname, s, [&] {
+      const hipError_t e2 = launch_r2c_wide2(b, g.w2_nctc, grid, lds, s);
+      return e2 != hipSuccess ? e2 : add_parts();
+    });
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
   if (!done && g.elem == ELEM_F16 && g.nd >= 2) {
     // every other plane (all but the widest mode counts and the shortest rows)
+    share(false);
     R2CArgs b = a;
     b.twS = pl->t.sgF;
     b.segph = pl->t.sgPh;
     b.lut_sat = pl->t.actSat;
-    hipError_t e = timed(kname, s, [&] { return launch_r2c_any(b, g.nct, pl->num_cu, s); });
+    hipError_t e = timed(kname, s, [&] {
+      const hipError_t e2 = launch_r2c_any(b, g.nct, pl->num_cu, s);
+      return e2 != hipSuccess ? e2 : add_parts();
+    });
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
@@ -1281,6 +1358,7 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
   a.cIc = pl->t.cIc;
   a.sIc = pl->t.sIc;
   a.lut = pl->t.lutGrad;
+  a.parts = 1;
   const char* kname = !x_epi              ? "c2r_plane"
                       : g.act == ACT_TANH ? "c2r_plane_tanh_grad"
                       : g.act == ACT_CLIP ? "c2r_plane_clip_grad"
@@ -1346,8 +1424,9 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     b.twI = pl->t.twI2;
     b.Kap = g.w2_kah;
     b.lut_sat = pl->t.gradSat;
+    b.parts = plane_parts(pl, a.planes, true);
     const size_t lds = c2r_wide2_lds_bytes(g.w2_nctc, g.w2_kah / 32, x_epi != nullptr, b.lut_sat);
-    const int grid = (int)std::min<int64_t>(a.planes, (int64_t)pl->num_cu);
+    const int grid = (int)std::min<int64_t>(a.planes * b.parts, (int64_t)pl->num_cu);
     hipError_t e = timed(kname, s, [&] { return launch_c2r_wide2(b, g.w2_nctc, grid, lds, s); });
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
@@ -1356,6 +1435,7 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     C2RArgs b = a;
     b.twS = pl->t.sgI;
     b.segph = pl->t.sgPh;
+    b.parts = plane_parts(pl, a.planes, false);
     hipError_t e = timed(kname, s, [&] { return launch_c2r_any(b, g.nct, pl->num_cu, s); });
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
@@ -2122,7 +2202,9 @@ fno_status fwd_impl(const fno_conv_desc* d, const void* x, const fno_weights* w,
   } flag(!build_plan);
   auto spectra = [&]() -> fno_status {
     fno_status r = run_sigma_stats(pl, x, bounds, s);
-    return r != FNO_OK ? r : run_r2c(pl, x, xh, inter, g.Cin, 1, 0, s, bounds);
+    if (r != FNO_OK) return r;
+    return run_r2c(pl, x, xh, inter, g.Cin, 1, 0, s, bounds,
+                   spare_output(d, pl, y, g.Cout, x, g.Cin, nullptr, 0, w, x_hat_out, nullptr));
   };
   if (d->weight_kind == FNO_WEIGHT_DENSE) {
     if ((st = spectra()) != FNO_OK) return st;
@@ -2292,7 +2374,10 @@ fno_status fno_spectral_conv_bwd_data(const fno_conv_desc* d, const void* x,
   void* gh = gy_hat_out ? gy_hat_out : (void*)gs;
   auto spectra = [&]() -> fno_status {
     fno_status r = run_sigma_stats(pl, x, bounds, s);
-    return r != FNO_OK ? r : run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s);
+    if (r != FNO_OK) return r;
+    return run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s, nullptr,
+                   spare_output(d, pl, gx, g.Cin, gy, g.Cout, pre_on ? x : nullptr, g.Cin, w,
+                                gy_hat_out, nullptr));
   };
   if (d->weight_kind == FNO_WEIGHT_DENSE) {
     if ((st = spectra()) != FNO_OK) return st;
@@ -2413,6 +2498,13 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
   char* xs = cache ? nullptr : base + L.add(spec_bytes(g, g.Cin));
   char* wsd = base + L.add(ws_bytes(d, pl, FNO_OP_BWD_DATA, true));
   void* gh = gy_hat_out ? gy_hat_out : (void*)gs;
+  // gx's memory for one of the forward transforms (both of x and gy are read
+  // until the last of them)
+  auto spare = [&](const void* in, int64_t c) {
+    const bool other_x = in != x;
+    return spare_output(d, pl, gx, g.Cin, in, c, other_x ? x : gy, other_x ? g.Cin : g.Cout, w, x_hat,
+                        gy_hat_out);
+  };
   if (tucker) {
     // the data part's regions inside wsd, laid out as in bwd_data (its first
     // region, the gradient spectrum, is unused: gh holds it), then the
@@ -2459,8 +2551,9 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
     auto side_b = [&](hipStream_t st_) { return wgrad(WG_SPECTRA, st_, pwb); };
     auto spectra = [&]() -> fno_status {
       fno_status r = run_sigma_stats(pl, x, bounds, s);
-      if (r == FNO_OK) r = run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s);
-      if (r == FNO_OK && !cache) r = run_r2c(pl, x, xs, inter, g.Cin, 1, 0, s, bounds);
+      if (r == FNO_OK) r = run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s, nullptr, spare(gy, g.Cout));
+      if (r == FNO_OK && !cache)
+        r = run_r2c(pl, x, xs, inter, g.Cin, 1, 0, s, bounds, spare(x, g.Cin));
       return r;
     };
     auto data_part = [&](SideStream*) -> fno_status {
@@ -2482,10 +2575,12 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
   if (pre_on && (st = run_sigma_stats(pl, x, bounds, s)) != FNO_OK) return st;
   const void* xh = x_hat;
   if (!cache) {
-    if ((st = run_r2c(pl, x, xs, inter, g.Cin, 1, 0, s, bounds)) != FNO_OK) return st;
+    if ((st = run_r2c(pl, x, xs, inter, g.Cin, 1, 0, s, bounds, spare(x, g.Cin))) != FNO_OK)
+      return st;
     xh = xs;
   }
-  if ((st = run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s)) != FNO_OK) return st;
+  if ((st = run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s, nullptr, spare(gy, g.Cout))) != FNO_OK)
+    return st;
   ContractArgs a{};
   a.zeros = pl->t.zeros;
   a.in = gh;

@@ -71,7 +71,7 @@ __device__ __forceinline__ int ob_col(int x) { return x ^ ((x & 32) >> 3); }
 // X[t_a][t_b] += sum_r (cB - i sB)[rc][t][r] Y_rc[r][t_b] over the items of
 // the plane, t_a = 2t + rc, t_b = 2 t' + cls.
 // ---------------------------------------------------------------------------
-template <int NCTC, bool PRE, bool EARLY>
+template <int NCTC, bool PRE, bool EARLY, bool SHARE>
 __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
   typedef MM<_Float16> M;
   constexpr int KBPC = NCTC * 8;               // complex columns per class (padded)
@@ -106,7 +106,9 @@ __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
   const int64_t plane_bytes = (int64_t)a.Na * a.Nb * 2;
   const int nks = Nh / W2_KS;      // a multiple of 4 on this path
   const int ngr = nks / 2;         // twiddle slices per item (even)
-  const int nch = NhA / W2_H;
+  // (SHARE: a.parts above 1; the index arithmetic costs the kernel 4% otherwise)
+  const uint32_t parts = SHARE ? (uint32_t)a.parts : 1u;
+  const int nch = NhA / W2_H / (int)parts;
   // step-B share of this wave: row tile q = (class rc, tile ta), column tiles
   // tb0 + j tbs over both column classes
   const int nta = a.Kap16 >> 4;    // leading-axis tiles per class (1, 2 or 4)
@@ -114,11 +116,19 @@ __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
   const int q = wave % nq, tb0 = wave / nq, tbs = W2_WAVES / nq;
   const int rc = q / nta, ta = q % nta;
 
-  const int64_t nitems = a.planes > (int64_t)blockIdx.x
-                             ? ((a.planes - 1 - blockIdx.x) / gridDim.x + 1) * nch
-                             : 0;
-  auto item_plane = [&](int64_t it) { return (int64_t)blockIdx.x + (it / nch) * gridDim.x; };
-  auto item_chunk = [&](int64_t it) { return (int)(it % nch) * W2_H; };
+  // a plane's items are shared by a.parts work-groups (1 unless there are too
+  // few planes): v = plane parts + part takes the part's nch items in order
+  const int64_t nv = a.planes * parts;
+  const int64_t nitems =
+      nv > (int64_t)blockIdx.x ? ((nv - 1 - blockIdx.x) / gridDim.x + 1) * nch : 0;
+  auto item_v = [&](int64_t it) { return (uint32_t)(blockIdx.x + (it / nch) * gridDim.x); };
+  auto item_plane = [&](int64_t it) {
+    return SHARE ? (int64_t)(item_v(it) / parts) : (int64_t)blockIdx.x + (it / nch) * gridDim.x;
+  };
+  auto item_first = [&](int64_t it) { return it % nch == 0; };
+  auto item_chunk = [&](int64_t it) {
+    return (int)((SHARE ? item_v(it) % parts * nch : 0u) + it % nch) * W2_H;
+  };
 
   // lane part of the row offset (the upper half's rows and the row's second
   // half go in the scalar offset), formed where it is used
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
   if (nitems > 0) {
     ldTW(0, twr[0]);
     ldTW(1, twr[1]);
-    const int rb = row_lane(0);
+    const int rb = row_lane(item_chunk(0));
 #pragma unroll
     for (int d = 0; d < 4; ++d) ldA(rs, rb, d, va[d]);
     stTW(twr[0], 0);
@@ -176,7 +186,7 @@ __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
   for (int64_t it = 0; it < nitems; ++it) {
     const int64_t p = item_plane(it);
     const int c0 = item_chunk(it);
-    if (c0 == 0) {
+    if (SHARE ? item_first(it) : c0 == 0) {
 #pragma unroll
       for (int j = 0; j < NTBW; ++j) accR[j] = accI[j] = f4zero();
     }
@@ -307,7 +317,21 @@ __global__ __launch_bounds__(W2_NT, 1) void r2c_wide2_kernel(R2CArgs a) {
     }
     __syncthreads();
 
-    if (c0 + W2_H >= NhA) {  // last item of the plane: store its spectrum
+    if (SHARE && item_first(it + 1)) {
+      // last item of the part: its sums, unscaled in fp32, to be added in order
+      f2* part = reinterpret_cast<f2*>(a.part) + (int64_t)item_v(it) * a.Ka * a.Kb;
+#pragma unroll
+      for (int j = 0; j < NTBW; ++j) {
+        const int jt = tb0 + j * tbs;
+        if (jt >= NTBW) continue;
+        const int t_b = 2 * ((jt % NTBC) * 16 + r16) + jt / NTBC;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int t_a = 2 * (ta * 16 + 4 * g + i) + rc;
+          if (t_a < a.Ka && t_b < a.Kb) part[t_a * a.Kb + t_b] = f2{accR[j][i], accI[j][i]};
+        }
+      }
+    } else if (!SHARE && c0 + W2_H >= NhA) {  // last item of the plane: store its spectrum
       const __amdgpu_buffer_rsrc_t ro = plane_rsrc(a.out, p, (int64_t)a.Ka * a.Kb * 4);
       int tq = ta * 16 + 4 * g;
       asm volatile("" : "+v"(tq));
@@ -417,14 +441,20 @@ __global__ __launch_bounds__(W2_NT, 1) void c2r_wide2_kernel(C2RArgs a) {
   const int Nh = a.Nb >> 1, NhA = a.Na >> 1;
   const int64_t plane_bytes = (int64_t)a.Na * a.Nb * 2;
   const int spec_bytes = a.Ka * a.Kb * 4;
-  const int nch = NhA / W2_H;
+  const int nch = NhA / W2_H / a.parts;
   const int nmb = Nh / MB;             // even on this path
   const int nq = a.Ka * a.Kb / 4;      // 16-byte spectrum pieces
-  const int64_t nitems = a.planes > (int64_t)blockIdx.x
-                             ? ((a.planes - 1 - blockIdx.x) / gridDim.x + 1) * nch
-                             : 0;
-  auto item_plane = [&](int64_t it) { return (int64_t)blockIdx.x + (it / nch) * gridDim.x; };
-  auto item_chunk = [&](int64_t it) { return (int)(it % nch) * W2_H; };
+  // a plane's items are shared by a.parts work-groups (1 unless there are too
+  // few planes): v = plane parts + part takes the part's nch items in order
+  const int64_t nv = a.planes * a.parts;
+  const int64_t nitems =
+      nv > (int64_t)blockIdx.x ? ((nv - 1 - blockIdx.x) / gridDim.x + 1) * nch : 0;
+  auto item_v = [&](int64_t it) { return (uint32_t)(blockIdx.x + (it / nch) * gridDim.x); };
+  auto item_plane = [&](int64_t it) { return (int64_t)(item_v(it) / (uint32_t)a.parts); };
+  auto item_first = [&](int64_t it) { return it % nch == 0; };
+  auto item_chunk = [&](int64_t it) {
+    return (int)((item_v(it) % (uint32_t)a.parts) * nch + it % nch) * W2_H;
+  };
 
   // the padding of ZT stays zero: every plane writes the same positions
   for (int i = tid; i < 2 * 2 * 2 * KBPC * LDZ; i += W2_NT) ZT[i] = (_Float16)0.0f;
@@ -527,7 +557,7 @@ __global__ __launch_bounds__(W2_NT, 1) void c2r_wide2_kernel(C2RArgs a) {
   u32x4 xr[2][2][2];
   if (nitems > 0) {
     ldZ(item_plane(0), zq);
-    ldC(0, cf, sf);
+    ldC(item_chunk(0), cf, sf);
     ldTW(0, twr[0]);
     if (TWA == 2) ldTW(1, twr[TWA - 1]);
     if (EPI) {
@@ -543,7 +573,7 @@ __global__ __launch_bounds__(W2_NT, 1) void c2r_wide2_kernel(C2RArgs a) {
     const bool more = it + 1 < nitems;
     const int64_t pn = more ? item_plane(it + 1) : p;
     const int cn = more ? item_chunk(it + 1) : c0;
-    if (c0 == 0) {
+    if (item_first(it)) {
       stZ(zq);
       __syncthreads();
     }
@@ -714,7 +744,7 @@ __global__ __launch_bounds__(W2_NT, 1) void c2r_wide2_kernel(C2RArgs a) {
     ldC(cn, cf, sf);
     block(nmb - 1, 1);
     // otherwise after the plane's last block
-    if (more && cn == 0 && !z_early) ldZ(pn, zq);
+    if (more && item_first(it + 1) && !z_early) ldZ(pn, zq);
   }
 }
 
@@ -745,10 +775,12 @@ size_t c2r_wide2_lds_bytes(int nctc, int nkzh, bool epi, int lut_sat) {
 
 template <int NCTC, bool PRE, bool EARLY>
 static hipError_t r2c_wide2_go(const R2CArgs& a, int grid, size_t lds, hipStream_t s) {
-  const void* k = (const void*)&r2c_wide2_kernel<NCTC, PRE, EARLY>;
-  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  auto k = a.parts > 1 ? r2c_wide2_kernel<NCTC, PRE, EARLY, true>
+                       : r2c_wide2_kernel<NCTC, PRE, EARLY, false>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((r2c_wide2_kernel<NCTC, PRE, EARLY>), dim3(grid), dim3(W2_NT), lds, s, a);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(W2_NT), lds, s, a);
   return hipGetLastError();
 }
 
