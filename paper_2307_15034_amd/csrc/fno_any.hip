@@ -598,10 +598,11 @@ hipError_t launch_part_sum(const void* part, void* out, int parts, int64_t plane
 int any_nk(int Nb) { return Nb <= 64 ? 2 : 4; }
 
 namespace {
-// waves that share a plane: one per 32 rows, up to the whole work-group
-int waves_log2(int Na) {
+// waves that share a plane: one per 32 rows, up to the whole work-group, and
+// more where that leaves compute units without a work-group
+int waves_log2(int Na, int64_t planes, int num_cu) {
   int lw = 0;
-  while (lw < 3 && (32 << lw) < Na) ++lw;
+  while (lw < 3 && ((32 << lw) < Na || (planes << lw) < (int64_t)AN_NW * num_cu)) ++lw;
   return lw;
 }
 }  // namespace
@@ -611,7 +612,7 @@ hipError_t launch_r2c_any(const R2CArgs& a_in, int nct, int num_cu, hipStream_t 
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap16 > 128)
     return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
-  a.lw = waves_log2(a.Na);
+  a.lw = waves_log2(a.Na, a.planes, num_cu);
   const bool pre = a.do_tanh != 0;
   size_t lds = any_r2c_lds(nct, nk, a.lw, pre, a.lut_sat);
   const size_t tab = (size_t)2 * a.Kap16 * (a.NaC + 8) * 2;
@@ -646,7 +647,7 @@ hipError_t launch_c2r_any(const C2RArgs& a_in, int nct, int num_cu, hipStream_t 
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap > 128)
     return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
-  a.lw = waves_log2(a.Na);
+  a.lw = waves_log2(a.Na, a.planes, num_cu);
   while (a.lw < 3 && any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0) > 160 * 1024) ++a.lw;
   size_t lds = any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0);
   const size_t tab = (size_t)2 * a.Na * (a.Kap + 8) * 2;

@@ -59,6 +59,7 @@ struct R2CArgs {
   // [planes][parts][Ka][Kb], which launch_part_sum adds
   int parts;
   void* part;
+  int foldA, foldB;   // fno_any32.hip: leading and last axis folded (even extents)
 };
 
 // Inverse of the above: spectrum [planes][Ka][Kb] -> y [planes][Na][Nb],
@@ -99,6 +100,7 @@ struct C2RArgs {
   int lw;
   int tab_lds;
   int parts;          // work-groups that share a plane's rows, as in R2CArgs
+  int foldA, foldB;
 };
 
 // Transforms of 1-D fp16 signals (fno_line.hip): S = planes signals of N
@@ -307,6 +309,14 @@ hipError_t launch_part_sum(const void* part, void* out, int parts, int64_t plane
 int any_nk(int Nb);  // k-steps of 32 columns in a segment of the last axis
 hipError_t launch_r2c_any(const R2CArgs& a, int nct, int num_cu, hipStream_t s);
 hipError_t launch_c2r_any(const C2RArgs& a, int nct, int num_cu, hipStream_t s);
+
+// fp32 planes of any extents (fno_any32.hip), nct = 2 * (padded modes) / 16 of
+// its own tables; hipErrorNotSupported when the shape is not one of the path's.
+__host__ __device__ constexpr int any32_nf(int kbp) { return kbp <= 32 ? 64 : 32; }  // columns of a segment
+hipError_t launch_r2c_any32(const R2CArgs& a, int nct, int num_cu, hipStream_t s);
+hipError_t launch_c2r_any32(const C2RArgs& a, int nct, int num_cu, hipStream_t s);
+hipError_t launch_part_sum32(const void* part, void* out, int parts, int64_t planes, int64_t K,
+                             float scale, hipStream_t s);
 
 // Radix-2 wide-plane transforms (fno_wide2.hip): the radix-2 tables in the
 // table fields; hipErrorNotSupported when the shape is not one of the path's.

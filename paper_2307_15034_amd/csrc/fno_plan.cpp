@@ -345,6 +345,9 @@ struct Geo {
   // of 256): column tiles per class, leading-axis tiles per class, and the
   // leading-axis slots per class padded to 32
   int w2, w2_nctc, w2_nta, w2_kah;
+  // fp32 planes of any extents: folded axes, padded modes, leading-axis slots
+  // padded to 16 (per class when folded) and rows padded to a block
+  int f3, f3_fa, f3_fb, f3_kbp, f3_kap, f3_rows;
 };
 
 struct DevTables {
@@ -358,6 +361,7 @@ struct DevTables {
   const void *twA2, *cB2, *sB2, *cI2, *sI2, *twI2;  // radix-2 wide-plane tables
   const void *lnF, *lnRow, *lnBlk, *lnI;            // 1-D fp16 signals
   const void *sgF, *sgI, *sgPh;                     // fp16 planes of any extents
+  const void *f3F, *f3I, *f3Ph, *f3cB, *f3sB, *f3cI, *f3sI;  // fp32 planes of any extents
 };
 
 struct Plan {
@@ -445,6 +449,14 @@ Geo make_geo(const fno_conv_desc* d) {
     g.w2_nctc = kbe <= 16 ? 2 : 4;
     g.w2_nta = nta <= 1 ? 1 : nta <= 2 ? 2 : 4;
     g.w2_kah = (int)round_up(m, 32);
+  }
+  g.f3 = g.elem == ELEM_F32 && nd >= 2 && g.Nb >= 8 && g.Kb <= 64;
+  if (g.f3) {
+    g.f3_fa = g.Na % 2 == 0;
+    g.f3_fb = g.Nb % 2 == 0 && g.Kb > 16;
+    g.f3_kbp = g.f3_fb ? 2 * (g.Kb <= 32 ? 16 : 32) : g.Kbp;
+    g.f3_kap = g.f3_fa ? 2 * (int)round_up(g.Ka / 2, 16) : g.Kap16;
+    g.f3_rows = g.f3_fa ? (int)round_up(g.Na / 2, 16) : (int)round_up(g.Na, 32);
   }
   return g;
 }
@@ -674,6 +686,39 @@ void fill_tables(const fno_conv_desc* d, const Geo& g, std::vector<T>& buf,
         }
       }
   }
+  if (g.f3) {
+    // fp32 planes of any extents (fno_any32.hip): modes in tile order (folded:
+    // even ones, then odd), slots in class order (folded: even, then odd)
+    const int kbp = g.f3_kbp, kap = g.f3_kap, nf = any32_nf(kbp);
+    size_t sf = alloc((size_t)2 * kbp * nf), si = alloc((size_t)nf * 2 * kbp);
+    size_t sp = alloc((size_t)2 * kbp);
+    for (int c = 0; c < kbp; ++c) {
+      const int t = g.f3_fb ? 2 * (c % (kbp / 2)) + c / (kbp / 2) : c;
+      if (t >= g.Kb) continue;
+      double cv, sv;
+      for (int m = 0; m < nf; ++m) {
+        twiddle(t, m, g.Nb, &cv, &sv);
+        buf[sf + (size_t)c * nf + m] = buf[si + (size_t)m * 2 * kbp + c] = (T)cv;
+        buf[sf + (size_t)(kbp + c) * nf + m] = buf[si + (size_t)m * 2 * kbp + kbp + c] = (T)(-sv);
+      }
+      twiddle(t, nf, g.Nb, &cv, &sv);
+      buf[sp + 2 * c] = (T)cv;
+      buf[sp + 2 * c + 1] = (T)sv;
+    }
+    const int nr = g.f3_fa ? g.Na / 2 : g.Na;
+    size_t cb = alloc((size_t)kap * g.f3_rows), sb = alloc((size_t)kap * g.f3_rows);
+    size_t ci = alloc((size_t)nr * kap), si2 = alloc((size_t)nr * kap);
+    for (int c = 0; c < kap; ++c) {
+      const int t = g.f3_fa ? 2 * (c % (kap / 2)) + c / (kap / 2) : c;
+      if (t >= g.Ka) continue;
+      for (int r = 0; r < nr; ++r) {
+        double cv, sv;
+        twiddle(ka_of(t), r, g.Na, &cv, &sv);
+        buf[cb + (size_t)c * g.f3_rows + r] = buf[ci + (size_t)r * kap + c] = (T)cv;
+        buf[sb + (size_t)c * g.f3_rows + r] = buf[si2 + (size_t)r * kap + c] = (T)sv;
+      }
+    }
+  }
   if (nd == 1 && g.elem == ELEM_F16) {
     // 1-D signals (LineArgs): forward twiddles of 128 samples, fp32 phases of
     // the rows and blocks, inverse twiddles with (re, im) columns interleaved
@@ -836,6 +881,15 @@ fno_status build_tables(const fno_conv_desc* d, Plan* pl) {
     pl->t.sB2 = at(ix++);
     pl->t.cI2 = at(ix++);
     pl->t.sI2 = at(ix++);
+  }
+  if (pl->g.f3) {
+    pl->t.f3F = at(ix++);
+    pl->t.f3I = at(ix++);
+    pl->t.f3Ph = at(ix++);
+    pl->t.f3cB = at(ix++);
+    pl->t.f3sB = at(ix++);
+    pl->t.f3cI = at(ix++);
+    pl->t.f3sI = at(ix++);
   }
   if (pl->g.nd == 1 && pl->g.elem == ELEM_F16) {
     pl->t.lnF = at(ix++);
@@ -1092,12 +1146,22 @@ fno_status run_sigma_stats(const Plan* pl, const void* x, double* bounds, hipStr
 // radix-2 kernels split a plane's chunks of 256 rows evenly, the others any way.
 int plane_parts(const Plan* pl, int64_t planes, bool even) {
   const Geo& g = pl->g;
-  if (g.nd != 2 || g.elem != ELEM_F16 || planes * 2 > pl->num_cu) return 1;
+  if (g.nd != 2 || planes * 2 > pl->num_cu) return 1;
+  if (g.elem == ELEM_F32 && !g.f3) return 1;
   const int nch = (g.Na + 255) / 256;
   int parts = (int)std::min<int64_t>(nch, pl->num_cu / planes);
   while (even && nch % parts) --parts;
   if (!even) parts = (nch + (nch + parts - 1) / parts - 1) / ((nch + parts - 1) / parts);
   return parts;
+}
+
+// A call of few small planes, where the kernels' start-up is most of their
+// time: the generic kernels, a work-group per plane, are quicker there than the
+// ones for any extents (16 planes of 43 x 43 in fp16: inverse 6.4 against 8.7
+// us; 32 of 24 x 24 in fp32: forward 6.8 against 9.8, inverse 7.7 against 8.5;
+// from 2048 planes of 40 x 40 on they are slower, 15.2 against 12.4).
+bool few_small_planes(const Plan* pl, int64_t planes) {
+  return (int64_t)pl->g.Na * pl->g.Nb <= 4096 && planes <= pl->num_cu;
 }
 
 // Memory that a call may use before it writes its output there: the output
@@ -1203,7 +1267,8 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
   };
   auto add_parts = [&]() {
     if (a.parts == 1) return hipSuccess;
-    return launch_part_sum(a.part, a.out, a.parts, a.planes, g.K, a.scaleB, s);
+    return (g.elem == ELEM_F16 ? launch_part_sum : launch_part_sum32)(a.part, a.out, a.parts,
+                                                                      a.planes, g.K, a.scaleB, s);
   };
   if (a.planes > 0x7fffffff || (g.nd == 3 && g.B * C > 65535)) return FNO_ERR_UNSUPPORTED;
   bool done = sigma;
@@ -1275,7 +1340,7 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (!done && g.elem == ELEM_F16 && g.nd >= 2) {
+  if (!done && g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(pl, a.planes)) {
     // every other plane (all but the widest mode counts and the shortest rows)
     share(false);
     R2CArgs b = a;
@@ -1284,6 +1349,24 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     b.lut_sat = pl->t.actSat;
     hipError_t e = timed(kname, s, [&] {
       const hipError_t e2 = launch_r2c_any(b, g.nct, pl->num_cu, s);
+      return e2 != hipSuccess ? e2 : add_parts();
+    });
+    if (e == hipSuccess) done = true;
+    else if (e != hipErrorNotSupported) return hip_fail(e, kname);
+  }
+  if (!done && g.f3 && !few_small_planes(pl, a.planes)) {
+    share(false);
+    R2CArgs b = a;
+    b.twS = pl->t.f3F;
+    b.segph = pl->t.f3Ph;
+    b.cB = pl->t.f3cB;
+    b.sB = pl->t.f3sB;
+    b.Nap = g.f3_rows;
+    b.Kap16 = g.f3_kap;
+    b.foldA = g.f3_fa;
+    b.foldB = g.f3_fb;
+    hipError_t e = timed(kname, s, [&] {
+      const hipError_t e2 = launch_r2c_any32(b, g.f3_kbp / 8, pl->num_cu, s);
       return e2 != hipSuccess ? e2 : add_parts();
     });
     if (e == hipSuccess) done = true;
@@ -1431,12 +1514,26 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (g.elem == ELEM_F16 && g.nd >= 2) {
+  if (g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(pl, a.planes)) {
     C2RArgs b = a;
     b.twS = pl->t.sgI;
     b.segph = pl->t.sgPh;
     b.parts = plane_parts(pl, a.planes, false);
     hipError_t e = timed(kname, s, [&] { return launch_c2r_any(b, g.nct, pl->num_cu, s); });
+    if (e == hipSuccess) return FNO_OK;
+    if (e != hipErrorNotSupported) return hip_fail(e, kname);
+  }
+  if (g.f3 && !few_small_planes(pl, a.planes)) {
+    C2RArgs b = a;
+    b.twS = pl->t.f3I;
+    b.segph = pl->t.f3Ph;
+    b.cI = pl->t.f3cI;
+    b.sI = pl->t.f3sI;
+    b.Kap = g.f3_kap;
+    b.foldA = g.f3_fa;
+    b.foldB = g.f3_fb;
+    b.parts = plane_parts(pl, a.planes, false);
+    hipError_t e = timed(kname, s, [&] { return launch_c2r_any32(b, g.f3_kbp / 8, pl->num_cu, s); });
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }

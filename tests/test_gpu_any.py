@@ -16,8 +16,8 @@ if torch.cuda.is_available():
 
 CASES = [
     # (n, modes, B, Cin, Cout)
-    ((5, 8), (2, 3), 3, 3, 2),          # one piece per row, eight planes per work-group
-    ((33, 9), (3, 5), 2, 5, 3),         # second row block holds one row; Nyquist-free odd rows
+    ((5, 8), (2, 3), 30, 30, 20),       # one piece per row, eight planes per work-group
+    ((33, 9), (3, 5), 20, 20, 15),      # second row block holds one row; Nyquist-free odd rows
     ((64, 63), (17, 7), 2, 3, 3),       # two waves per plane, 34 leading slots
     ((65, 65), (8, 33), 1, 4, 3),       # second segment holds one column, four mode tiles
     ((127, 129), (24, 17), 3, 3, 4),    # four waves, 48 leading slots (three tiles)
