@@ -264,6 +264,36 @@ struct TriArgs {
   int c_ext, Nb;
 };
 hipError_t launch_tucker_tri(const TriArgs& g, hipStream_t s);
+
+// The CP weight gradient's steps that read no spectrum, mode index t
+// innermost, u_j[t_j][r] and lambda[r] in the storage type, the rest fp32
+// complex.  S[r][t] = lambda[r] prod_j u_j[t_j][r] is formed on the way.
+//   launch_cp_tri:  R[r][t] = sum_b P[b][r][t] Q[b][r][t],
+//                   Z1[b][r][t] = Q conj(S), Z2[b][r][t] = scale c(t) P conj(S);
+//   launch_cp_tail: g_lambda[r] = sum_t R prod_j conj(u_j),
+//                   g_u_j[t_j][r] = conj(lambda[r]) sum_{t without t_j} R
+//                                   prod_{q != j} conj(u_q)
+// (one or two axes, modes per rank within its bounds; hipErrorNotSupported
+// otherwise).
+struct CpArgs {
+  const void* P;
+  const void* Q;
+  void* R;
+  void* Z1;
+  void* Z2;
+  const void* lambda;
+  const void* u[3];
+  int elem;  // of lambda and u
+  int nd, B, rank;
+  int ext[3];
+  int64_t T;  // product of ext
+  float scale;
+  int Nb;
+  void* g_lambda;
+  void* g_u[3];
+};
+hipError_t launch_cp_tri(const CpArgs& g, hipStream_t s);
+hipError_t launch_cp_tail(const CpArgs& g, hipStream_t s);
 hipError_t launch_scale_complex(float* p, int64_t n, float s, hipStream_t st);
 
 // Persistent fp16 paths of small planes (up to 64 x 64); hipErrorNotSupported

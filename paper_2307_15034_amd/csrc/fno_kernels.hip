@@ -979,33 +979,44 @@ __global__ __launch_bounds__(256) void pair_kernel(PairArgs a) {
   pair_store(a, idx, cidx, sr, si);
 }
 
-// Products without a contracted index (elementwise and outer products):
-// PE_NV consecutive results along the innermost result index per thread,
-// decoded once; each is the same single product as in pair_kernel.  The
-// two results of a thread are stored with one access (16 bytes fp32, 8 bytes
-// fp16), so consecutive lanes write consecutive bytes and every store
-// instruction covers whole cache lines.
-constexpr int PE_NV = 2;
+// Products without a contracted index (elementwise and outer products): NV
+// consecutive results along the innermost result index per thread, decoded
+// once; each is the same single product as in pair_kernel.  All values are
+// loaded before the first is used, as one access where they are consecutive
+// (va, vb), and the results are stored with one access, so consecutive lanes
+// write consecutive bytes.
+template <int NV, typename C>
+__device__ __forceinline__ void ew_load(const void* p, int64_t off, int64_t st, int vec, C (&x)[NV]) {
+  const C* q = reinterpret_cast<const C*>(p) + off;
+  if (vec) {
+    struct __align__(NV * sizeof(C) < 16 ? NV * sizeof(C) : 16) V {
+      C c[NV];
+    };
+    const V v = *reinterpret_cast<const V*>(q);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) x[j] = v.c[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) x[j] = q[j * st];
+  }
+}
 
-__global__ __launch_bounds__(256) void pair_ew_kernel(PairArgs a, int64_t items) {
+template <int NV, typename CA, typename CB>
+__global__ __launch_bounds__(256) void pair_ew_kernel(PairArgs a, int64_t items, int va, int vb) {
   const int64_t it = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (it >= items) return;
-  const int64_t idx = it * PE_NV;
   int64_t ao, bo, cidx;
-  pair_decode(a, idx, ao, bo, cidx);
+  pair_decode(a, it * NV, ao, bo, cidx);
   const int kin = a.n_out - 1;
-  const int64_t sa = a.a_stride_out[kin], sb = a.b_stride_out[kin];
-  f2 x[PE_NV], y[PE_NV];
+  CA x[NV];
+  CB y[NV];
+  ew_load<NV, CA>(a.a, ao, a.a_stride_out[kin], va, x);
+  ew_load<NV, CB>(a.b, bo, a.b_stride_out[kin], vb, y);
+  float r[2 * NV];
 #pragma unroll
-  for (int j = 0; j < PE_NV; ++j) {
-    x[j] = load_elem(a.a, a.a_elem, ao + j * sa);
-    y[j] = load_elem(a.b, a.b_elem, bo + j * sb);
-  }
-  float r[2 * PE_NV];
-#pragma unroll
-  for (int j = 0; j < PE_NV; ++j) {
+  for (int j = 0; j < NV; ++j) {
     float sr = 0.0f, si = 0.0f;
-    pair_fma(a, x[j], y[j], sr, si);
+    pair_fma(a, f2{(float)x[j][0], (float)x[j][1]}, f2{(float)y[j][0], (float)y[j][1]}, sr, si);
     float s = a.scale;
     if (a.scale_c_axis >= 0) {
       const int64_t ci = kin == a.scale_c_axis ? cidx + j : cidx;
@@ -1015,11 +1026,44 @@ __global__ __launch_bounds__(256) void pair_ew_kernel(PairArgs a, int64_t items)
     r[2 * j + 1] = si * s;
   }
   if (a.out_elem == ELEM_F16) {
-    h4 v = {to_h(r[0]), to_h(r[1]), to_h(r[2]), to_h(r[3])};
-    reinterpret_cast<h4*>(a.out)[it] = v;
+    typedef _Float16 hv __attribute__((ext_vector_type(2 * NV)));
+    hv v;
+#pragma unroll
+    for (int j = 0; j < 2 * NV; ++j) v[j] = to_h(r[j]);
+    reinterpret_cast<hv*>(a.out)[it] = v;
   } else {
-    reinterpret_cast<f4*>(a.out)[it] = f4{r[0], r[1], r[2], r[3]};
+#pragma unroll
+    for (int j = 0; j < NV / 2; ++j)
+      reinterpret_cast<f4*>(a.out)[it * (NV / 2) + j] =
+          f4{r[4 * j], r[4 * j + 1], r[4 * j + 2], r[4 * j + 3]};
   }
+}
+
+// Four results per thread where the innermost extent allows it and the
+// results still fill the chip; pairs otherwise.
+template <int NV>
+void launch_ew(const PairArgs& a, hipStream_t s) {
+  const int64_t items = a.out_size / NV;
+  const dim3 grid((unsigned)((items + 255) / 256)), block(256);
+  // one access per operand: consecutive values, every other stride a multiple
+  // of NV and the base aligned to the access
+  const auto vec = [&](const void* p, const int64_t* st, int elem) {
+    const size_t bytes = std::min<size_t>(16, (size_t)NV * (elem == ELEM_F16 ? 4 : 8));
+    if (st[a.n_out - 1] != 1 || (uintptr_t)p % bytes != 0) return 0;
+    for (int k = 0; k + 1 < a.n_out; ++k)
+      if (st[k] % NV != 0) return 0;
+    return 1;
+  };
+  const int va = vec(a.a, a.a_stride_out, a.a_elem), vb = vec(a.b, a.b_stride_out, a.b_elem);
+  const bool ah = a.a_elem == ELEM_F16, bh = a.b_elem == ELEM_F16;
+  if (ah && bh)
+    hipLaunchKernelGGL((pair_ew_kernel<NV, h2, h2>), grid, block, 0, s, a, items, va, vb);
+  else if (ah)
+    hipLaunchKernelGGL((pair_ew_kernel<NV, h2, f2>), grid, block, 0, s, a, items, va, vb);
+  else if (bh)
+    hipLaunchKernelGGL((pair_ew_kernel<NV, f2, h2>), grid, block, 0, s, a, items, va, vb);
+  else
+    hipLaunchKernelGGL((pair_ew_kernel<NV, f2, f2>), grid, block, 0, s, a, items, va, vb);
 }
 
 // PB_NB results per thread along result index blk_k (absent from A): the
@@ -1353,11 +1397,13 @@ hipError_t launch_pair(const PairArgs& a_in, hipStream_t s) {
     div_magic((uint32_t)((a.out_ext[a.blk_k] + PB_NB - 1) / PB_NB), &a.blk_mag, &a.blk_shr);
   // Few results with long reductions (weight-gradient steps): a work-group
   // per result.  Otherwise a thread per PB_NB results or per result.
-  if (a.red_size == 1 && a.n_out > 0 && a.out_ext[a.n_out - 1] % PE_NV == 0 &&
-      a.out_size / PE_NV <= 0xffffffffll * 256) {
-    const int64_t items = a.out_size / PE_NV;
-    dim3 grid((unsigned)((items + 255) / 256)), block(256);
-    hipLaunchKernelGGL(pair_ew_kernel, grid, block, 0, s, a, items);
+  const bool ew = a.red_size == 1 && a.n_out > 0 && a.out_size <= 0x7fffffffll * 256 &&
+                  a.out_ext[a.n_out - 1] % 2 == 0;
+  if (ew && a.out_ext[a.n_out - 1] % 4 == 0 && ((uintptr_t)a.out & 15u) == 0 &&
+      a.out_size >= (int64_t)4 * 64 * 1024) {
+    launch_ew<4>(a, s);
+  } else if (ew) {
+    launch_ew<2>(a, s);
   } else if (a.red_size >= 2048 && a.out_size <= (int64_t)1 << 20) {
     dim3 grid((unsigned)a.out_size), block(256);
     hipLaunchKernelGGL(pair_block_kernel, grid, block, 0, s, a);

@@ -1979,11 +1979,10 @@ fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, 
                         hipStream_t s, size_t* scratch_used = nullptr, int phases = WG_ALL,
                         const WgradBranches* br = nullptr) {
   const bool dry = scratch_used != nullptr;
-  int phase = WG_WEIGHTS;  // the phase of the steps that follow
   WgradFork fk(s);
   auto pair = [&](const Sizes& sz_, const Opnd& A, const Opnd& Bo, const std::string& res,
                   void* out, float scale, int c_axis_char, hipStream_t st) -> fno_status {
-    if (dry || !(phases & phase)) return FNO_OK;
+    if (dry || !(phases & WG_SPECTRA)) return FNO_OK;
     return run_pair(sz_, A, Bo, res, out, ELEM_F32, scale, c_axis_char, pl->g.Nb, st,
                     fk.part(scratch, st));
   };
@@ -2008,21 +2007,9 @@ fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, 
   };
   auto U = [&](int j, int conj) { return Wt(w->u_mode[j], std::string(1, kSpatial[j]) + "r", conj); };
   fno_status r;
-  // ---- weights only: S[r, sp] = lambda[r] prod_j u_j[sp_j, r] ----
-  Opnd S = Wt(w->core, "r", 0);
-  {
-    std::string lab = "r";
-    for (int j = 0; j < nd; ++j) {
-      const std::string nl = lab + kSpatial[j];
-      void* dst = buf(nl);
-      if ((r = pair(sz, S, U(j, 0), nl, dst, 1.0f, 0, s))) return r;
-      S = F(dst, nl, 0);
-      lab = nl;
-    }
-  }
-  const Opnd Sc{S.ptr, S.lab, S.elem, 1};
+  // scratch of the workspace's layout that the fused products leave unused
+  for (int j = 0; j < nd; ++j) (void)buf("r" + sp.substr(0, j + 1));
   // ---- spectra ----
-  phase = WG_SPECTRA;
   const std::string lP = "br" + sp, lR = "r" + sp;
   void* P = buf(lP);
   void* Q = buf(lP);
@@ -2031,13 +2018,39 @@ fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, 
   void* Z2 = buf(lP);
   if ((r = pair(sz, Wt(xh, "bi" + sp, 1), Wt(w->u_in, "ir", 1), lP, P, 1.0f, 0, s))) return r;
   if ((r = pair(sz, Wt(gh, "bo" + sp, 0), Wt(w->u_out, "or", 1), lP, Q, sqN, clast, s))) return r;
-  if (!dry && (phases & WG_SPECTRA) && (r = fk.fork(br))) return r;
-  if ((r = pair(sz, F(Q, lP, 0), Sc, lP, Z1, 1.0f, 0, fk.z1))) return r;
+  // R, Z1 and Z2, with S[r, sp] = lambda[r] prod_j u_j[sp_j, r] on the way
+  CpArgs ca{};
+  ca.P = P;
+  ca.Q = Q;
+  ca.R = Rb;
+  ca.Z1 = Z1;
+  ca.Z2 = Z2;
+  ca.lambda = w->core;
+  ca.elem = g.elem;
+  ca.nd = nd;
+  ca.B = (int)sz['b'];
+  ca.rank = (int)sz['r'];
+  ca.T = label_size(sp, sz);
+  ca.scale = sqN;
+  ca.Nb = g.Nb;
+  ca.g_lambda = gw->core;
+  for (int j = 0; j < nd; ++j) {
+    ca.u[j] = w->u_mode[j];
+    ca.ext[j] = (int)sz[kSpatial[j]];
+    ca.g_u[j] = gw->u_mode[j];
+  }
+  const bool run = !dry && (phases & WG_SPECTRA);
+  if (run) FNO_HIP(timed("tucker_pair", s, [&] { return launch_cp_tri(ca, s); }));
+  if (run && (r = fk.fork(br))) return r;
   if ((r = pair(sz, Wt(xh, "bi" + sp, 1), F(Z1, lP, 0), "ir", gw->u_in, 1.0f, 0, fk.z1))) return r;
-  if ((r = pair(sz, F(P, lP, 0), Sc, lP, Z2, sqN, clast, fk.z2))) return r;
   if ((r = pair(sz, Wt(gh, "bo" + sp, 0), F(Z2, lP, 0), "or", gw->u_out, 1.0f, 0, fk.z2)))
     return r;
-  if ((r = pair(sz, F(P, lP, 0), F(Q, lP, 0), lR, Rb, 1.0f, 0, s))) return r;
+  if (run) {
+    // the chains of R in one launch where it takes them; one by one below
+    const hipError_t e = timed("tucker_pair", s, [&] { return launch_cp_tail(ca, s); });
+    if (e == hipSuccess) return FNO_OK;
+    if (e != hipErrorNotSupported) return hip_fail(e, "cp_tail");
+  }
   // g_lambda: contract R with conj(u_j) along every spatial axis
   {
     Opnd cur = F(Rb, lR, 0);
