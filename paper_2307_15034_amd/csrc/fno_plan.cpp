@@ -133,7 +133,12 @@ struct PStep {
   std::string res;
 };
 
-using Sizes = std::map<char, int64_t>;
+// A number per index letter (zero: none).
+struct Sizes {
+  int64_t v[26] = {};
+  int64_t& operator[](char c) { return v[c - 'a']; }
+  int64_t at(char c) const { return v[c - 'a']; }
+};
 
 int64_t label_size(const std::string& s, const Sizes& sz) {
   int64_t v = 1;
@@ -1593,7 +1598,7 @@ fno_status run_pair(const Sizes& sz, const Opnd& A0, const Opnd& B0, const std::
   a.conj_b = Bo.conj;
   a.out_elem = out_elem;
   auto strides = [&](const std::string& lab) {
-    std::map<char, int64_t> st;
+    Sizes st;
     int64_t acc = 1;
     for (int i = (int)lab.size() - 1; i >= 0; --i) {
       st[lab[i]] = acc;
@@ -1610,8 +1615,8 @@ fno_status run_pair(const Sizes& sz, const Opnd& A0, const Opnd& B0, const std::
     char c = res[k];
     a.out_ext[k] = sz.at(c);
     a.out_size *= a.out_ext[k];
-    a.a_stride_out[k] = sa.count(c) ? sa[c] : 0;
-    a.b_stride_out[k] = sb.count(c) ? sb[c] : 0;
+    a.a_stride_out[k] = sa.at(c);
+    a.b_stride_out[k] = sb.at(c);
     if (c == c_axis_char) a.scale_c_axis = k;
   }
   std::string red;
@@ -1624,8 +1629,8 @@ fno_status run_pair(const Sizes& sz, const Opnd& A0, const Opnd& B0, const std::
     char c = red[k];
     a.red_ext[k] = sz.at(c);
     a.red_size *= a.red_ext[k];
-    a.a_stride_red[k] = sa.count(c) ? sa[c] : 0;
-    a.b_stride_red[k] = sb.count(c) ? sb[c] : 0;
+    a.a_stride_red[k] = sa.at(c);
+    a.b_stride_red[k] = sb.at(c);
   }
   a.scale = scale;
   a.Nb = Nb;
@@ -1638,8 +1643,9 @@ fno_status run_pair(const Sizes& sz, const Opnd& A0, const Opnd& B0, const std::
 // Evaluate a Tucker or CP path: operands [spec, core (CP: lambda), u_in,
 // u_out, u_1..u_d].
 // Which steps of a factorised path a call runs: all of them; only those
-// whose operands all come from the weights (no spectrum), which then take no
-// split-K partial sums so that they may run beside the other steps; or the
+// whose operands all come from the weights (no spectrum), which never take
+// split-K partial sums, so that they may run beside the other steps and give
+// the same results where they do not; or the
 // others, the first of them that reads a weights-only result waiting for the
 // event `ready` (recorded after the weights-only steps on their stream).
 enum PathSteps { PATH_ALL = 0, PATH_WEIGHTS = 1, PATH_REST = 2 };
@@ -1731,7 +1737,7 @@ fno_status run_tucker_path(const fno_conv_desc* d, const Plan* pl, bool adjoint,
         if (e != hipSuccess) return hip_fail(e, "wait for the weights-only steps");
       }
       fno_status r = run_pair(sz, ops[ps.p], ops[ps.q], store, dst, oelem, 1.0f,
-                              last ? clast : 0, g.Nb, s, which == PATH_WEIGHTS ? nullptr : part);
+                              last ? clast : 0, g.Nb, s, wstep ? nullptr : part);
       if (r != FNO_OK) return r;
     }
     std::vector<Opnd> next;
@@ -2113,12 +2119,23 @@ fno_status check_weights(const fno_conv_desc* d, const fno_weights* w) {
 
 inline bool okptr(const void* p) { return p && aligned16(p); }
 
-// Workspace check from the host-only plan: runs before any device call.
+// Workspace check from the host-only plan, before anything is allocated or
+// enqueued.  The search for a factorised path's order (12 us) is taken from the
+// descriptor's plan when the current device has one.
 fno_status check_ws(const fno_conv_desc* d, fno_op op, bool caches, const void* ws,
                     size_t ws_len) {
+  std::shared_ptr<Plan> known;
+  if (factorized(d)) {
+    int dev = 0;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    if (!g_plans.empty() && hipGetDevice(&dev) == hipSuccess) {
+      auto it = g_plans.find(key_of(d, dev));
+      if (it != g_plans.end()) known = it->second;
+    }
+  }
   Plan hp;
-  host_plan(d, &hp);
-  if (ws_len < ws_bytes(d, &hp, op, caches)) return FNO_ERR_WORKSPACE_TOO_SMALL;
+  if (!known) host_plan(d, &hp);
+  if (ws_len < ws_bytes(d, known ? known.get() : &hp, op, caches)) return FNO_ERR_WORKSPACE_TOO_SMALL;
   if (!okptr(ws)) return FNO_ERR_INVALID_ARGUMENT;
   return FNO_OK;
 }
@@ -2160,10 +2177,9 @@ bool capturing(hipStream_t s) {
   return hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
 }
 
-// The device's side stream, or null (the caller then runs both parts on its
-// own stream): when it cannot be created, or must not be because `s` is
-// being captured.  Call with g_side_mutex held.
-SideStream* side_stream_locked(hipStream_t s) {
+// The device's side stream, or null when it cannot be created, or must not be
+// because `s` is being captured.  Call with g_side_mutex held.
+SideStream* side_stream_of_device(hipStream_t s) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
   auto it = g_side.find(dev);
@@ -2186,6 +2202,25 @@ SideStream* side_stream_locked(hipStream_t s) {
   return &(g_side[dev] = ss);
 }
 
+// The side stream for a call of `d`, or null (the caller then runs both parts
+// on its own stream), also where the fork would cost more than the overlap
+// gives.  Two streams and their events take 130 to 150 us of host time a step,
+// so a step launched from the host has to be long: Tucker weights with
+// B max(Cin, Cout) N of 13.8 M points 300 to 350 us forked, 278 on one stream;
+// 33 M 290 to 350 against 322; 67 M 336 to 369 against 398; 134 M 594 against
+// 704.  CP weights have little beside the transforms: 270 to 320 against 242
+// at 33 M, 785 against 753 at 67 M, 711 against 701 at 134 M.  Recorded into a
+// graph the fork costs the device alone: 0.5 M points 149 to 189 us forked and
+// 106 to 165 on one stream, 17 M 262 and 288, 134 M (CP) 672 and 704.
+SideStream* side_stream_locked(const fno_conv_desc* d, hipStream_t s) {
+  SideStream* ss = side_stream_of_device(s);
+  if (!ss) return nullptr;
+  const int64_t points = d->batch * std::max<int64_t>(d->c_in, d->c_out) * nspatial(d);
+  const bool pays = capturing(s) ? points >= (int64_t)1 << 23
+                                 : d->weight_kind != FNO_WEIGHT_CP && points >= (int64_t)1 << 25;
+  return pays ? ss : nullptr;
+}
+
 // Two branches after the work already on `s`: on the caller's stream
 // first() then second(side); on the side stream side_a(side, stream), which
 // reads nothing first() writes, and then side_b(stream), which reads
@@ -2197,9 +2232,9 @@ SideStream* side_stream_locked(hipStream_t s) {
 // from the host one by one, its few large kernels start while the side's
 // many small ones are still being enqueued.
 template <typename FA, typename F1, typename FB, typename F2>
-fno_status run_forked(hipStream_t s, FA side_a, F1 first, FB side_b, F2 second) {
+fno_status run_forked(const fno_conv_desc* d, hipStream_t s, FA side_a, F1 first, FB side_b, F2 second) {
   std::unique_lock<std::mutex> lk(g_side_mutex);
-  SideStream* ss = side_stream_locked(s);
+  SideStream* ss = side_stream_locked(d, s);
   fno_status st;
   if (!ss) {
     lk.unlock();
@@ -2257,7 +2292,7 @@ fno_status run_path_forked(const fno_conv_desc* d, const Plan* pl, bool adjoint,
   SideStream* ss = nullptr;
   if (allow_side && path_has_weight_steps(path, 4 + (size_t)d->ndim)) {
     lk.lock();
-    ss = side_stream_locked(s);
+    ss = side_stream_locked(d, s);
     if (!ss) lk.unlock();
   }
   hipError_t e = ss ? hipEventRecord(ss->fork, s) : hipSuccess;
@@ -2566,7 +2601,7 @@ fno_status fno_spectral_conv_bwd_weight(const fno_conv_desc* d, const void* x, c
   }
   // the chains after P and Q on the side streams when they exist
   std::unique_lock<std::mutex> lk(g_side_mutex);
-  SideStream* ss = capturing(s) ? nullptr : side_stream_locked(s);
+  SideStream* ss = capturing(s) ? nullptr : side_stream_locked(d, s);
   WgradBranches wb{};
   if (ss) wb = ss->branches();
   const WgradBranches* b = ss ? &wb : nullptr;
@@ -2673,7 +2708,7 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
       const float sc = (float)(1.0 / std::sqrt((double)g.N));
       return run_c2r(pl, gxs, gx, inter, g.Cin, sc, pre_on ? x : nullptr, s, bounds);
     };
-    return run_forked(s, side_a, spectra, side_b, data_part);
+    return run_forked(d, s, side_a, spectra, side_b, data_part);
   }
   // dense: the data part's regions inside wsd, laid out as in bwd_data (its
   // first region, the gradient spectrum, is unused: gh holds it)
