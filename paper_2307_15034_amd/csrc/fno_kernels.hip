@@ -484,7 +484,11 @@ __global__ __launch_bounds__(256) void axis_kernel(AxisArgs a) {
 // <= 128, inner a multiple of 4): the twiddle table is staged in LDS next to
 // the data (no global loads between the products), and the 16-row x 64-column
 // result tiles are staged in LDS too, so that every store instruction writes
-// whole 256-byte row segments (consecutive lanes, consecutive 16 bytes).
+// whole 256-byte row segments (consecutive lanes, consecutive 16 bytes).  One
+// wave of work-groups at the sizes in use, so bound by the latency of a tile:
+// all of its loads are issued at once (128 x 64 rows of 512, 16.8 MB: 11.7 us with
+// a load and its scattered 2-byte writes at a time, 10.5 here; 64 x 100 rows of
+// 128: 13.4 and 10.7).
 size_t axis_f16_lds_bytes(int Linp, int Lout16) {
   const int ldl = Linp + 8;
   return (size_t)2 * 64 * ldl * 2 + (size_t)2 * Lout16 * ldl * 2 + (size_t)Lout16 * 68 * 4;
@@ -510,24 +514,58 @@ __global__ __launch_bounds__(256) void axis_f16_kernel(AxisArgs a) {
   const _Float16* er = reinterpret_cast<const _Float16*>(a.er);
   const _Float16* ei = reinterpret_cast<const _Float16*>(a.ei);
 
-  // table: [NTT*16][Linp] twice, 16-byte pieces; data: Linp rows x 16 quads
-  const int tpr = a.Linp / 8;
-  for (int i = tid; i < 2 * NTT * 16 * tpr; i += 256) {
-    const int tab = i / (NTT * 16 * tpr), rem = i - tab * (NTT * 16 * tpr);
-    const int t = rem / tpr, c = (rem - t * tpr) * 8;
-    const h8 v = *reinterpret_cast<const h8*>((tab ? ei : er) + (int64_t)t * a.Linp + c);
-    *reinterpret_cast<h8*>((tab ? Ei : Er) + t * ldl + c) = v;
-  }
-  for (int idx = tid; idx < a.Linp * 16; idx += 256) {
-    const int l = idx >> 4, jj = (idx & 15) * 4;
-    h8 v = M::zero();
-    if (l < a.Lin && j0 + jj < a.inner)
-      v = *reinterpret_cast<const h8*>(in + ((int64_t)l * a.inner + j0 + jj) * 2);
+  // Data: a thread takes four rows l of four columns, the four loads in flight
+  // at once, turns the block in registers and writes four l of a column at a
+  // time.  Eight lanes along the columns (128-byte rows) by eight along the row
+  // quads spread the writes over all banks.  Rows past Lin are zero; columns
+  // past the end repeat the last ones and are not stored.
+  const int nlq = a.Linp / 4;
+  const uint32_t* inw = reinterpret_cast<const uint32_t*>(in);
+  const auto fetch = [&](int v, u32x4 (&x)[4]) {
+    const int l = 4 * ((v >> 3) % nlq), c = (v & 7) + 8 * ((v >> 3) / nlq);
+    const int j = min(j0 + 4 * c, a.inner - 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      x[i] = *reinterpret_cast<const u32x4*>(inw + (int64_t)min(l + i, a.Lin - 1) * a.inner + j);
+  };
+  const auto put = [&](int v, const u32x4 (&x)[4]) {
+    const int l = 4 * ((v >> 3) % nlq), c = (v & 7) + 8 * ((v >> 3) / nlq);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      Ir[(jj + e) * ldl + l] = v[2 * e];
-      Ii[(jj + e) * ldl + l] = v[2 * e + 1];
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = l + i < a.Lin ? x[i][e] : 0u;
+      *reinterpret_cast<u32x2*>(Ir + (4 * c + e) * ldl + l) =
+          u32x2{__builtin_amdgcn_perm(w[1], w[0], 0x05040100u),
+                __builtin_amdgcn_perm(w[3], w[2], 0x05040100u)};
+      *reinterpret_cast<u32x2*>(Ii + (4 * c + e) * ldl + l) =
+          u32x2{__builtin_amdgcn_perm(w[1], w[0], 0x07060302u),
+                __builtin_amdgcn_perm(w[3], w[2], 0x07060302u)};
     }
+  };
+  u32x4 x[4];
+  const int items = nlq * 16;
+  if (tid < items) fetch(tid, x);
+  // table: [NTT*16][Linp] twice, 16-byte pieces, in batches of loads
+  const int tpr = a.Linp / 8, half = NTT * 16 * tpr;
+  for (int i0 = tid; i0 < 2 * half; i0 += 4 * 256) {
+    h8 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + 256 * u, 2 * half - 1), tab = i >= half, rem = i - tab * half;
+      v[u] = *reinterpret_cast<const h8*>((tab ? ei : er) + (int64_t)rem * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 256 * u, tab = i >= half, rem = i - tab * half;
+      const int t = rem / tpr, c = (rem - t * tpr) * 8;
+      if (i < 2 * half) *reinterpret_cast<h8*>((tab ? Ei : Er) + t * ldl + c) = v[u];
+    }
+  }
+  if (tid < items) put(tid, x);
+  for (int v = tid + 256; v < items; v += 256) {
+    fetch(v, x);
+    put(v, x);
   }
   __syncthreads();
   // D[t][j] = sum_l E[t][l] X[l][j]; wave owns columns 16 wave .. + 16
