@@ -36,6 +36,7 @@
 #include <vector>
 
 #include "fno_device.h"
+#include "fno_gemm_offsets.h"
 
 namespace fno {
 
@@ -115,8 +116,8 @@ __device__ __forceinline__ f4 mfma_h(h8 a, h8 b, f4 c) {
 // zeroing of what lies outside) behind them that would wait for each one in
 // turn, so all loads of two stages are in flight at once.  Every load is
 // unconditional: rows outside the result read row 0 of the class and the
-// offset table repeats its last entry past the chunk; such elements are
-// zeroed on the way to LDS.  With 64 or more rows a thread takes four
+// offset table repeats its last quad past the chunk (gemm_k_entry), so that
+// each lies inside the operand; such elements are zeroed on the way to LDS.  With 64 or more rows a thread takes four
 // consecutive k of one row (four loads, or one where they are consecutive in
 // memory) and writes them to LDS as one 16-byte (fp32) or 8-byte (fp16)
 // access; lanes run along the row's k quads (kfast) or along the rows.
@@ -326,12 +327,12 @@ __global__ __launch_bounds__(256) void pair_gemm_kernel(GemmArgs g) {
     noR[i] = orr;
     nmul[i] = mu;
   }
-  // whole stages of offsets: entries past the chunk repeat its last one
+  // whole stages of offsets: entries past the chunk repeat its last quad
   for (int i = tid; i < nst * TK; i += 256) {
     int32_t oa, ob;
     int64_t orr;
     float mu;
-    cls_decode(g.c[CL_K], (uint32_t)(kb + min(i, klen - 1)), g.Nb, oa, ob, orr, mu);
+    cls_decode(g.c[CL_K], (uint32_t)(kb + gemm_k_entry(i, klen)), g.Nb, oa, ob, orr, mu);
     koA[i] = oa;
     koB[i] = ob;
   }
