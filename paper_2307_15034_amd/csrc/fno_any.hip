@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "fno_device.h"
+#include "fno_routes.h"
 
 namespace fno {
 
@@ -597,22 +598,12 @@ hipError_t launch_part_sum(const void* part, void* out, int parts, int64_t plane
 // columns of a segment, in k-steps: 128 unless the row is that short
 int any_nk(int Nb) { return Nb <= 64 ? 2 : 4; }
 
-namespace {
-// waves that share a plane: one per 32 rows, up to the whole work-group, and
-// more where that leaves compute units without a work-group
-int waves_log2(int Na, int64_t planes, int num_cu) {
-  int lw = 0;
-  while (lw < 3 && ((32 << lw) < Na || (planes << lw) < (int64_t)AN_NW * num_cu)) ++lw;
-  return lw;
-}
-}  // namespace
-
 hipError_t launch_r2c_any(const R2CArgs& a_in, int nct, int num_cu, hipStream_t s) {
   R2CArgs a = a_in;
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap16 > 128)
     return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
-  a.lw = waves_log2(a.Na, a.planes, num_cu);
+  a.lw = share_waves_log2((a.Na + 31) / 32, a.planes, num_cu);
   const bool pre = a.do_tanh != 0;
   size_t lds = any_r2c_lds(nct, nk, a.lw, pre, a.lut_sat);
   const size_t tab = (size_t)2 * a.Kap16 * (a.NaC + 8) * 2;
@@ -647,7 +638,7 @@ hipError_t launch_c2r_any(const C2RArgs& a_in, int nct, int num_cu, hipStream_t 
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap > 128)
     return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
-  a.lw = waves_log2(a.Na, a.planes, num_cu);
+  a.lw = share_waves_log2((a.Na + 31) / 32, a.planes, num_cu);
   while (a.lw < 3 && any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0) > 160 * 1024) ++a.lw;
   size_t lds = any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0);
   const size_t tab = (size_t)2 * a.Na * (a.Kap + 8) * 2;

@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "fno_device.h"
+#include "fno_routes.h"
 
 namespace fno {
 
@@ -521,16 +522,8 @@ hipError_t launch_part_sum32(const void* part, void* out, int parts, int64_t pla
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-namespace {
-// waves that share a plane: one per block of 32 rows (16 pairs of folded
-// ones), more where that leaves compute units without a work-group
-int f3_lw(int Na, bool fa, int64_t planes, int num_cu) {
-  const int nblk = fa ? (Na / 2 + 15) / 16 : (Na + 31) / 32;
-  int lw = 0;
-  while (lw < 3 && ((1 << lw) < nblk || (planes << lw) < (int64_t)F3_NW * num_cu)) ++lw;
-  return lw;
-}
-}  // namespace
+// blocks of 32 rows (16 pairs of folded ones) of a plane
+static int f3_blocks(int Na, bool fold) { return fold ? (Na / 2 + 15) / 16 : (Na + 31) / 32; }
 
 #define FNO_F3_DISPATCH(KERN, NCTV)                                                       \
   switch ((a.foldA ? 2 : 0) + (a.foldB ? 1 : 0)) {                                        \
@@ -544,7 +537,7 @@ hipError_t launch_r2c_any32(const R2CArgs& a_in, int nct, int num_cu, hipStream_
   R2CArgs a = a_in;
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 4 >= (PLANE_OOB >> 1) || a.Kap16 > 128)
     return hipErrorNotSupported;
-  a.lw = f3_lw(a.Na, a.foldA, a.planes, num_cu);
+  a.lw = share_waves_log2(f3_blocks(a.Na, a.foldA), a.planes, num_cu);
   while (a.lw < 3 && f3_r2c_lds(nct, a.lw) > 160 * 1024) ++a.lw;
   size_t lds = f3_r2c_lds(nct, a.lw);
   if (lds > 160 * 1024) return hipErrorNotSupported;
@@ -575,7 +568,7 @@ hipError_t launch_c2r_any32(const C2RArgs& a_in, int nct, int num_cu, hipStream_
   C2RArgs a = a_in;
   if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 4 >= (PLANE_OOB >> 1) || a.Kap > 128)
     return hipErrorNotSupported;
-  a.lw = f3_lw(a.Na, a.foldA, a.planes, num_cu);
+  a.lw = share_waves_log2(f3_blocks(a.Na, a.foldA), a.planes, num_cu);
   while (a.lw < 3 && f3_c2r_lds(nct, a.lw, a.Kap) > 160 * 1024) ++a.lw;
   size_t lds = f3_c2r_lds(nct, a.lw, a.Kap);
   if (lds > 160 * 1024) return hipErrorNotSupported;
