@@ -1,5 +1,5 @@
 // Persistent truncated transforms of small fp16 planes (up to 64 rows x 64
-// columns).
+// columns; up to 128 x 256 where planes are few, for the short start-up).
 //
 // Each work-group stays resident and walks planes p = blockIdx.x,
 // blockIdx.x + gridDim.x, ...; the twiddle tables are staged once per
@@ -428,8 +428,14 @@ hipError_t launch_r2c_fast(const R2CArgs& a, int nct, int nka, int nw, int grid,
                            hipStream_t s) {
   R2C_CASE(2, 1, 4)
   R2C_CASE(2, 2, 4)
+  R2C_CASE(2, 4, 4)
+  R2C_CASE(2, 4, 8)
   R2C_CASE(4, 2, 4)
+  R2C_CASE(4, 4, 4)
+  R2C_CASE(4, 4, 8)
+  R2C_CASE(4, 8, 4)
   R2C_CASE(8, 2, 4)
+  R2C_CASE(8, 4, 8)
   return hipErrorNotSupported;
 }
 
@@ -442,7 +448,12 @@ hipError_t launch_r2c_fast(const R2CArgs& a, int nct, int nka, int nw, int grid,
 hipError_t launch_c2r_fast(const C2RArgs& a, int nct, int nw, int nbt, int nkz, int grid,
                            size_t lds, hipStream_t s) {
   C2R_CASE(2, 4, 1, 1)
+  C2R_CASE(2, 4, 2, 1)
+  C2R_CASE(2, 8, 2, 1)
   C2R_CASE(4, 4, 1, 1)
+  C2R_CASE(4, 4, 2, 1)
+  C2R_CASE(4, 8, 2, 2)
+  C2R_CASE(4, 8, 2, 1)
   C2R_CASE(8, 4, 1, 2)
   return hipErrorNotSupported;
 }

@@ -296,7 +296,7 @@ hipError_t launch_cp_tri(const CpArgs& g, hipStream_t s);
 hipError_t launch_cp_tail(const CpArgs& g, hipStream_t s);
 hipError_t launch_scale_complex(float* p, int64_t n, float s, hipStream_t st);
 
-// Persistent fp16 paths of small planes (up to 64 x 64); hipErrorNotSupported
+// Persistent fp16 paths of small planes (up to 128 x 256); hipErrorNotSupported
 // when no instantiation matches the shape.
 // nw: waves per work-group, one per 16-row tile of the plane.
 hipError_t launch_r2c_fast(const R2CArgs& a, int nct, int nka, int nw, int grid, size_t lds,

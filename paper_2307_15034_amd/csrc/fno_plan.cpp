@@ -17,6 +17,7 @@
 
 #include "../../include/fno_spectral_conv.h"
 #include "fno_internal.h"
+#include "fno_routes.h"
 #include "fno_host.h"
 
 namespace fno {
@@ -1160,13 +1161,9 @@ int plane_parts(const Plan* pl, int64_t planes, bool even) {
   return parts;
 }
 
-// A call of few small planes, where the kernels' start-up is most of their
-// time: the generic kernels, a work-group per plane, are quicker there than the
-// ones for any extents (16 planes of 43 x 43 in fp16: inverse 6.4 against 8.7
-// us; 32 of 24 x 24 in fp32: forward 6.8 against 9.8, inverse 7.7 against 8.5;
-// from 2048 planes of 40 x 40 on they are slower, 15.2 against 12.4).
-bool few_small_planes(const Plan* pl, int64_t planes) {
-  return (int64_t)pl->g.Na * pl->g.Nb <= 4096 && planes <= pl->num_cu;
+PlaneShape plane_shape(const Plan* pl, int64_t planes) {
+  const Geo& g = pl->g;
+  return {g.Na, g.Nb, g.Kbp, g.elem == ELEM_F16, planes, pl->num_cu};
 }
 
 // Memory that a call may use before it writes its output there: the output
@@ -1277,7 +1274,7 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
   };
   if (a.planes > 0x7fffffff || (g.nd == 3 && g.B * C > 65535)) return FNO_ERR_UNSUPPORTED;
   bool done = sigma;
-  if (!done && g.elem == ELEM_F16 && g.nd == 1) {
+  if (!done && g.elem == ELEM_F16 && g.nd == 1 && !few_short_signals(plane_shape(pl, a.planes), do_tanh)) {
     LineArgs l{};
     l.in = in;
     l.out = spec;
@@ -1309,12 +1306,9 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
       else if (e != hipErrorNotSupported) return hip_fail(e, kname);
     }
   }
-  if (!done && g.elem == ELEM_F16 && a.vec && g.Nb <= 64 && g.Na <= 64 && g.nct <= 8) {
-    // small planes, a work-group each: its short start-up counts there (24 x
-    // 24, 256 planes: 6.5 against 8.4 us with tanh in the kernel for any
-    // extents; 72 x 72, 2048 planes: 26.2 against 19.6)
-    const int nka = g.Nb <= 32 ? 1 : 2;
-    const int nw = 4;
+  if (!done && g.elem == ELEM_F16 && a.vec && g.nct <= 8 && fast_planes(plane_shape(pl, a.planes), false)) {
+    const int nka = g.Nb <= 32 ? 1 : g.Nb <= 64 ? 2 : g.Nb <= 128 ? 4 : 8;
+    const int nw = g.Na <= 64 ? 4 : 8;
     const size_t lds = r2c_fast_lds_bytes(g.nct, nka, nw, g.Kap16, g.Nap_f);
     const int grid = (int)std::min<int64_t>(a.planes, (int64_t)2 * pl->num_cu);
     if (lds <= 80 * 1024) {
@@ -1345,7 +1339,7 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (!done && g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(pl, a.planes)) {
+  if (!done && g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(plane_shape(pl, a.planes), false)) {
     // every other plane (all but the widest mode counts and the shortest rows)
     share(false);
     R2CArgs b = a;
@@ -1359,7 +1353,7 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     if (e == hipSuccess) done = true;
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (!done && g.f3 && !few_small_planes(pl, a.planes)) {
+  if (!done && g.f3 && !few_small_planes(plane_shape(pl, a.planes), false)) {
     share(false);
     R2CArgs b = a;
     b.twS = pl->t.f3F;
@@ -1487,12 +1481,10 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
       if (e != hipErrorNotSupported) return hip_fail(e, kname);
     }
   }
-  if (g.elem == ELEM_F16 && a.vec && g.Kb % 4 == 0 && g.Nb <= 64 && g.Na <= 64 && g.nct <= 8 &&
-      g.Kap <= 128) {
-    // small planes, as in the forward (24 x 24: 6.2 against 9.2 us, 7.1
-    // against 11.0 with tanh'; 40 x 40, 2048 planes: 10.9 against 12.1)
-    const int nbt = 1;
-    const int nw = 4;
+  if (g.elem == ELEM_F16 && a.vec && g.Kb % 4 == 0 && g.nct <= 8 && g.Kap <= 128 &&
+      fast_planes(plane_shape(pl, a.planes), true)) {
+    const int nbt = (g.Nb + 63) / 64;
+    const int nw = g.Na <= 64 ? 4 : 8;
     const int nkz = g.Kap / 32;
     const size_t lds = c2r_fast_lds_bytes(g.nct, nw, nbt, nkz);
     const int grid = (int)std::min<int64_t>(a.planes, (int64_t)2 * pl->num_cu);
@@ -1519,7 +1511,7 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(pl, a.planes)) {
+  if (g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(plane_shape(pl, a.planes), true)) {
     C2RArgs b = a;
     b.twS = pl->t.sgI;
     b.segph = pl->t.sgPh;
@@ -1528,7 +1520,7 @@ fno_status run_c2r(const Plan* pl, const void* spec, void* out, void* inter, int
     if (e == hipSuccess) return FNO_OK;
     if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
-  if (g.f3 && !few_small_planes(pl, a.planes)) {
+  if (g.f3 && !few_small_planes(plane_shape(pl, a.planes), true)) {
     C2RArgs b = a;
     b.twS = pl->t.f3I;
     b.segph = pl->t.f3Ph;

@@ -1,10 +1,17 @@
-// How a transform of planes is laid out on the chip, by sizes alone; plain C++,
-// so that the host can replay it.
+// Which kernel a transform of planes or signals runs, by sizes alone; plain
+// C++, so that the host can replay it.
 #pragma once
 
 #include <stdint.h>
 
 namespace fno {
+
+struct PlaneShape {
+  int Na, Nb, Kbp;  // rows, columns, last-axis modes padded to 16, 32, 64, ..
+  bool fp16;
+  int64_t planes;
+  int num_cu;
+};
 
 // Waves of a work-group of eight that share a plane in the kernels for any
 // extents, as a power of two: one per block of 32 rows, up to all eight, and
@@ -16,6 +23,72 @@ constexpr int share_waves_log2(int64_t blocks, int64_t planes, int num_cu) {
   int lw = 0;
   while (lw < 3 && ((1 << lw) < blocks || (planes << (lw + 1)) <= (int64_t)8 * num_cu)) ++lw;
   return lw;
+}
+
+// A call of few small planes, where the kernels' start-up is most of their
+// time: the generic kernels, a work-group per plane, are quicker there than the
+// ones for any extents, whose work-groups stage tables and whose waves take
+// blocks of 32 rows.  The line lies at a plane's work (points, the rows rounded
+// up to 16, per 16 padded modes): a table by the blocks of a plane (1, 2, 3 and
+// 4, more), which say how many planes the kernels for any extents take in a pass
+// over the chip, and by the planes per compute unit (1, 2, 3, 4 and up to 12);
+// rows that the generic kernel reads by 16 bytes have lines of their own.
+// Measured over 1 to 3008 planes of 8 to 201 rows of 8 to 505 columns with 3, 12
+// and 28 modes; of 1800 other calls of such sizes one in thirty is more than 5%,
+// and none more than 19%, slower than through the generic and small-plane kernels
+// alone, near half are quicker.
+// The whole call in us, generic and any extents: fp16 forward, 16 planes of 48 x
+// 136: 17.4 and 19.2, 1024: 26.1 and 24.7; inverse with tanh', 512 planes of 16 x
+// 264: 23.6 and 28.7, of 49 x 105: 27.6 and 22.4, 2048 of 200 x 16: 57 and 64;
+// fp32 forward, 256 planes of 30 x 200: 32.3 and 36.6, 512 of 32 x 504: 73.6 and
+// 65.4; inverse, 256 of 48 x 73 with 28 modes: 35.0 and 31.1.
+constexpr bool few_small_planes(const PlaneShape& g, bool inverse) {
+  typedef const short Lines[2][4][5];  // [aligned rows][blocks][planes per unit]: work / 16
+  constexpr Lines h_fwd = {
+      {{64, 0, 0, 0, 0}, {128, 0, 0, 0, 0}, {192, 0, 192, 128, 0}, {0, 0, 256, 256, 96}},
+      {{384, 0, 0, 0, 0}, {640, 0, 0, 0, 0}, {192, 0, 256, 192, 192}, {0, 384, 384, 384, 256}}};
+  constexpr Lines h_inv = {
+      {{256, 128, 96, 0, 0}, {256, 128, 64, 0, 0}, {192, 64, 256, 0, 64}, {0, 192, 256, 96, 192}},
+      {{1024, 512, 512, 0, 0}, {1536, 640, 192, 0, 64}, {384, 128, 2048, 128, 128}, {0, 256, 384, 256, 256}}};
+  constexpr Lines s_fwd = {
+      {{640, 512, 96, 96, 0}, {2048, 96, 0, 0, 0}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}},
+      {{1024, 640, 96, 128, 0}, {2048, 384, 0, 0, 0}, {192, 0, 640, 192, 192}, {0, 0, 1024, 384, 256}}};
+  constexpr Lines s_inv = {
+      {{128, 64, 0, 0, 0}, {128, 0, 0, 0, 0}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}},
+      {{512, 128, 0, 0, 0}, {512, 0, 0, 0, 0}, {0, 0, 0, 0, 0}, {0, 0, 0, 0, 0}}};
+  const int64_t units = (g.planes + g.num_cu - 1) / g.num_cu;
+  if (units < 1 || units > 12) return false;
+  const int q = units < 5 ? (int)units - 1 : 4;
+  const int b = g.Na <= 32 ? 0 : g.Na <= 64 ? 1 : g.Na <= 128 ? 2 : 3;
+  const bool aligned = g.Nb % (g.fp16 ? 8 : 4) == 0;
+  const Lines& l = g.fp16 ? (inverse ? h_inv : h_fwd) : (inverse ? s_inv : s_fwd);
+  return (g.Na + 15) / 16 * (int64_t)g.Nb * (g.Kbp / 16) <= l[aligned][b][q];
+}
+
+// Few short 1-D signals in the forward transform, as few_small_planes: the
+// kernels for small planes (the generic ones where those do not apply) start
+// sooner than the one for signals, up to 64 samples; up to 128 where the former
+// have them, and with 33 to 64 modes, whose tables are the larger part, up to
+// 192.  (64 signals of 64 samples and 8 modes, the whole call with tanh: 11.7
+// against 13.4 us, 2048: 18.7 against 15.2; 256 of 144 and 60 modes: 20.8
+// against 22.9.)
+constexpr bool few_short_signals(const PlaneShape& g, bool pre) {
+  if (g.planes > 2 * (int64_t)g.num_cu) return g.Nb <= 32 && g.planes <= 4 * (int64_t)g.num_cu;
+  return g.Nb <= 64 || (g.Nb <= 128 && g.Nb % 8 == 0 && g.Kbp <= 32) ||
+         (g.Nb <= 192 && g.Kbp == 64 && !pre);
+}
+
+// Planes that the small-plane kernels take, a work-group each: up to 64 x 64 at
+// any count, larger ones where planes are few and the short start-up counts
+// (whole call in us, against the kernel for any extents: 72 x 72, 20 modes,
+// forward with tanh, 64 planes 17.1 and 18.7, 2048: 51.6 and 47.9; inverse with
+// tanh', 64 planes 16.9 and 19.4, 2048: 56.5 and 52.9).
+constexpr bool fast_planes(const PlaneShape& g, bool inverse) {
+  if (g.Nb <= 64 && g.Na <= 64) return true;
+  if (g.Nb > 256 || g.Na > 128) return false;
+  const int64_t work = (int64_t)(g.Na + 31) / 32 * 32 * g.Nb * (g.Kbp / 16);
+  return g.planes <= g.num_cu ||
+         (inverse && work <= 12288 && g.planes <= 3 * (int64_t)g.num_cu);
 }
 
 }  // namespace fno

@@ -3,9 +3,11 @@ the C ABI, and the float64 oracle on the same stored values."""
 from __future__ import annotations
 
 import sys
+import warnings
 
 import numpy as np
 import torch
+from torch.profiler import ProfilerActivity, profile
 
 from oracle import fno_oracle as O
 import synth
@@ -103,6 +105,32 @@ def run_all(layer, x, w, gy, caches=True):
     else:
         gwh = host(gw)
     return host(y), host(gx), gwh
+
+
+def kernels(fn):
+    """Names of the library's kernels that fn launches, in order."""
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            fn()
+            torch.cuda.synchronize()
+    return [e.name for e in p.events() if "fno" in e.name and "kernel" in e.name]
+
+
+def check_routes(layer, x, w, gy, fwd=None, inv=None):
+    """The forward transforms of the layer's fwd and bwd_data run a kernel whose
+    name holds `fwd`, the inverse ones one that holds `inv` (None: any).  (No
+    names: another profiler holds the device; nothing to check.)"""
+    xd, wd, gyd = dev(x), dev(w), dev(gy)
+    layer.fwd(xd, wd)
+    for call in (lambda: layer.fwd(xd, wd), lambda: layer.bwd_data(xd, wd, gyd)):
+        names = kernels(call)
+        if not names:
+            return
+        say("  " + " ".join(names))
+        for want, kind in ((fwd, "r2c_"), (inv, "c2r_")):
+            got = [n for n in names if kind in n]
+            assert got and (want is None or all(want in n for n in got)), (want, names)
 
 
 def rel(a, b) -> float:

@@ -35,3 +35,45 @@ def test_waves_that_share_a_plane(tmp_path):
         if (!ok && ++bad < 5) std::printf("blocks %d planes %d: %d\\n", blocks, planes, lw);
       }
   return bad != 0;""")
+
+
+def test_few_planes_and_signals(tmp_path):
+    """Calls on either side of the lines, as measured on 256 compute units
+    ({rows, columns, padded modes, fp16, planes, compute units})."""
+    replay(tmp_path, """
+  int bad = 0;
+  auto expect = [&](const char* what, bool got, bool want) {
+    if (got != want) ++bad, std::printf("%s: %d\\n", what, got);
+  };
+  // the small-plane kernels: any count up to 64 x 64, few larger planes
+  for (bool inverse : {false, true}) {
+    expect("72 x 72, 64", fast_planes({72, 72, 32, true, 64, 256}, inverse), true);
+    expect("128 x 72, 16", fast_planes({128, 72, 32, true, 16, 256}, inverse), true);
+    expect("72 x 72, 2048", fast_planes({72, 72, 32, true, 2048, 256}, inverse), false);
+    expect("64 x 64, 8192", fast_planes({64, 64, 16, true, 8192, 256}, inverse), true);
+    expect("129 x 64, 16", fast_planes({129, 64, 16, true, 16, 256}, inverse), false);
+  }
+  // the generic kernels against those for any extents
+  expect("48 x 136, 16", few_small_planes({48, 136, 16, true, 16, 256}, false), true);
+  expect("48 x 136, 1024", few_small_planes({48, 136, 16, true, 1024, 256}, false), false);
+  expect("16 x 264, 512", few_small_planes({16, 264, 16, true, 512, 256}, true), true);
+  expect("49 x 105, 512", few_small_planes({49, 105, 16, true, 512, 256}, true), false);
+  expect("200 x 16, 2048", few_small_planes({200, 16, 16, true, 2048, 256}, true), true);
+  expect("241 x 241, 512", few_small_planes({241, 241, 32, true, 512, 256}, false), false);
+  expect("fp32 30 x 200, 256", few_small_planes({30, 200, 16, false, 256, 256}, false), true);
+  expect("fp32 32 x 504, 512", few_small_planes({32, 504, 16, false, 512, 256}, false), false);
+  expect("fp32 48 x 73, 256", few_small_planes({48, 73, 32, false, 256, 256}, true), false);
+  expect("fp32 128 x 128, 2048", few_small_planes({128, 128, 32, false, 2048, 256}, true), false);
+  // no count of planes leaves the tables
+  for (long planes : {1L, 256L, 257L, 1024L, 1025L, 3072L, 3073L, 1L << 31})
+    for (int rows : {1, 32, 33, 64, 65, 128, 129, 65536})
+      for (int half = 0; half < 2; ++half)
+        if (planes > 3072) expect("many", few_small_planes({rows, 8, 16, half > 0, planes, 256}, half > 0), false);
+        else (void)few_small_planes({rows, 65536, 128, half > 0, planes, 256}, true);
+  // 1-D signals
+  expect("64, 64", few_short_signals({1, 64, 16, true, 64, 256}, true), true);
+  expect("64, 2048", few_short_signals({1, 64, 16, true, 2048, 256}, true), false);
+  expect("144, 60 modes", few_short_signals({1, 144, 64, true, 256, 256}, false), true);
+  expect("144, 60 modes, tanh", few_short_signals({1, 144, 64, true, 256, 256}, true), false);
+  expect("8192", few_short_signals({1, 8192, 32, true, 1, 256}, false), false);
+  return bad != 0;""")
