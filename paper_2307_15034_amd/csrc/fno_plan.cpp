@@ -1750,7 +1750,7 @@ fno_status run_tucker_path(const fno_conv_desc* d, const Plan* pl, bool adjoint,
   return FNO_OK;
 }
 
-// Phases of the factorised weight gradients: the steps that read only the
+// Phases of the Tucker weight gradient: the steps that read only the
 // weights (partial products of the core and the mode factors), and the
 // steps that read the spectra.  Every phase lays out the scratch the same
 // way, so the two may run as separate calls in order.
@@ -1974,13 +1974,13 @@ size_t tucker_wgrad_bytes(const fno_conv_desc* d, const Plan* pl) {
 //   g_u_in = sum_{b,sp} conj(Xhat) (Q conj(S)),  g_u_out = sum_{b,sp} G' (P conj(S)).
 fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, const void* gh,
                         const fno_weights* w, fno_weight_grads* gw, char* scratch,
-                        hipStream_t s, size_t* scratch_used = nullptr, int phases = WG_ALL,
-                        const WgradBranches* br = nullptr) {
+                        hipStream_t s, const WgradBranches* br = nullptr,
+                        size_t* scratch_used = nullptr) {
   const bool dry = scratch_used != nullptr;
   WgradFork fk(s);
   auto pair = [&](const Sizes& sz_, const Opnd& A, const Opnd& Bo, const std::string& res,
                   void* out, float scale, int c_axis_char, hipStream_t st) -> fno_status {
-    if (dry || !(phases & WG_SPECTRA)) return FNO_OK;
+    if (dry) return FNO_OK;
     return run_pair(sz_, A, Bo, res, out, ELEM_F32, scale, c_axis_char, pl->g.Nb, st,
                     fk.part(scratch, st));
   };
@@ -2005,9 +2005,6 @@ fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, 
   };
   auto U = [&](int j, int conj) { return Wt(w->u_mode[j], std::string(1, kSpatial[j]) + "r", conj); };
   fno_status r;
-  // scratch of the workspace's layout that the fused products leave unused
-  for (int j = 0; j < nd; ++j) (void)buf("r" + sp.substr(0, j + 1));
-  // ---- spectra ----
   const std::string lP = "br" + sp, lR = "r" + sp;
   void* P = buf(lP);
   void* Q = buf(lP);
@@ -2037,13 +2034,12 @@ fno_status run_cp_wgrad(const fno_conv_desc* d, const Plan* pl, const void* xh, 
     ca.ext[j] = (int)sz[kSpatial[j]];
     ca.g_u[j] = gw->u_mode[j];
   }
-  const bool run = !dry && (phases & WG_SPECTRA);
-  if (run) FNO_HIP(timed("tucker_pair", s, [&] { return launch_cp_tri(ca, s); }));
-  if (run && (r = fk.fork(br))) return r;
+  if (!dry) FNO_HIP(timed("tucker_pair", s, [&] { return launch_cp_tri(ca, s); }));
+  if (!dry && (r = fk.fork(br))) return r;
   if ((r = pair(sz, Wt(xh, "bi" + sp, 1), F(Z1, lP, 0), "ir", gw->u_in, 1.0f, 0, fk.z1))) return r;
   if ((r = pair(sz, Wt(gh, "bo" + sp, 0), F(Z2, lP, 0), "or", gw->u_out, 1.0f, 0, fk.z2)))
     return r;
-  if (run) {
+  if (!dry) {
     // the chains of R in one launch where it takes them; one by one below
     const hipError_t e = timed("tucker_pair", s, [&] { return launch_cp_tail(ca, s); });
     if (e == hipSuccess) return FNO_OK;
@@ -2091,7 +2087,7 @@ size_t cp_wgrad_bytes(const fno_conv_desc* d, const Plan* pl) {
   fno_weight_grads gw{};
   size_t used = 0;
   char dummy = 0;
-  (void)run_cp_wgrad(d, pl, &dummy, &dummy, &w, &gw, &dummy, nullptr, &used);
+  (void)run_cp_wgrad(d, pl, &dummy, &dummy, &w, &gw, &dummy, nullptr, nullptr, &used);
   return used;
 }
 
@@ -2598,7 +2594,7 @@ fno_status fno_spectral_conv_bwd_weight(const fno_conv_desc* d, const void* x, c
   if (ss) wb = ss->branches();
   const WgradBranches* b = ss ? &wb : nullptr;
   if (d->weight_kind == FNO_WEIGHT_CP)
-    return run_cp_wgrad(d, pl, xh, gh, w, gw, tsc, s, nullptr, WG_ALL, b);
+    return run_cp_wgrad(d, pl, xh, gh, w, gw, tsc, s, b);
   return run_tucker_wgrad(d, pl, xh, gh, w, gw, tsc, s, nullptr, WG_ALL, b);
 }
 
@@ -2654,15 +2650,12 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
     char* tsc = wsd + Ld.total;
     double* bounds = (double*)(wsd + ws_core(d, pl, FNO_OP_BWD_DATA, true));
     const void* xh = x_hat ? x_hat : (const void*)xs;
-    // The weight gradient writes only its own scratch and gw; its steps
-    // that read only the weights run beside the transforms of gy (and x),
-    // the rest beside the adjoint path and the inverse transform.
+    // The weight gradient writes only its own scratch and gw; Tucker weights'
+    // steps that read only the weights run beside the transforms of gy (and x)
+    // (CP weights have none), the rest beside the adjoint path and the inverse
+    // transform.
     WgradBranches wb{};
-    auto wgrad = [&](int phases, hipStream_t st_, const WgradBranches* b) {
-      return d->weight_kind == FNO_WEIGHT_CP
-                 ? run_cp_wgrad(d, pl, xh, gh, w, gw, wsw, st_, nullptr, phases, b)
-                 : run_tucker_wgrad(d, pl, xh, gh, w, gw, wsw, st_, nullptr, phases, b);
-    };
+    const bool cp = d->weight_kind == FNO_WEIGHT_CP;
     // the side first takes the adjoint path's weights-only steps, which the
     // caller's stream waits for before the first step that reads them
     hipEvent_t ready = nullptr;
@@ -2683,9 +2676,13 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
         wb.z1 = wb.z2 = s;
         pwb = &wb;
       }
-      return r != FNO_OK ? r : wgrad(WG_WEIGHTS, st_, nullptr);
+      if (r != FNO_OK || cp) return r;
+      return run_tucker_wgrad(d, pl, xh, gh, w, gw, wsw, st_, nullptr, WG_WEIGHTS, nullptr);
     };
-    auto side_b = [&](hipStream_t st_) { return wgrad(WG_SPECTRA, st_, pwb); };
+    auto side_b = [&](hipStream_t st_) {
+      return cp ? run_cp_wgrad(d, pl, xh, gh, w, gw, wsw, st_, pwb)
+                : run_tucker_wgrad(d, pl, xh, gh, w, gw, wsw, st_, nullptr, WG_SPECTRA, pwb);
+    };
     auto spectra = [&]() -> fno_status {
       fno_status r = run_sigma_stats(pl, x, bounds, s);
       if (r == FNO_OK) r = run_r2c(pl, gy, gh, inter, g.Cout, 0, 1, s, nullptr, spare(gy, g.Cout));

@@ -285,6 +285,18 @@ def test_preactivation_descriptor_checks():
         assert B.fno_spectral_conv_workspace_size(d, B.FNO_OP_FWD) > 0
 
 
+def test_cp_weight_gradient_workspace_holds_what_its_kernels_use():
+    """Scratch of a 1-D CP weight gradient grows with the rank by the rows of
+    P, Q, Z1, Z2 (per sample) and R, in fp32 complex values, and nothing else."""
+    bt, m = 4, 32
+
+    def size(rank):
+        d = B.make_desc((256,), (m,), bt, 8, 8, B.FNO_PREC_FP16_TANH, B.FNO_WEIGHT_CP, (rank,))
+        return B.fno_spectral_conv_workspace_size(d, B.FNO_OP_BWD_WEIGHT)
+
+    assert size(24) - size(16) == 8 * m * 8 * (4 * bt + 1)
+
+
 def test_sigma_clip_workspace_holds_the_bounds():
     """The statistics-based clip adds 16 bytes (lo, hi in double) per (batch,
     input channel) plane, rounded up to 256, to the workspaces of the calls
