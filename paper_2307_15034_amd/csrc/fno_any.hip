@@ -642,14 +642,12 @@ hipError_t launch_c2r_any(const C2RArgs& a_in, int nct, int num_cu, hipStream_t 
   while (a.lw < 3 && any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0) > 160 * 1024) ++a.lw;
   size_t lds = any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0);
   const size_t tab = (size_t)2 * a.Na * (a.Kap + 8) * 2;
-  const int per_cu = 1;
-  a.tab_lds = lds + tab <= (size_t)160 * 1024 / per_cu;
+  a.tab_lds = lds + tab <= (size_t)160 * 1024;
   if (a.tab_lds) lds += tab;
   if (lds > 160 * 1024) return hipErrorNotSupported;
   const int64_t ngrp = AN_NW >> a.lw;
   const int grid = a.parts > 1 ? (int)a.planes * a.parts
-                               : (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp,
-                                                        (int64_t)per_cu * num_cu);
+                               : (int)std::min<int64_t>((a.planes + ngrp - 1) / ngrp, num_cu);
 #define FNO_ANY_I(N, K)                                                                   \
   if (nct == N && nk == K) {                                                              \
     auto k = a.parts > 1 ? (a.epilogue ? c2r_any_kernel<N, K, true, true>                 \
