@@ -600,8 +600,7 @@ int any_nk(int Nb) { return Nb <= 64 ? 2 : 4; }
 
 hipError_t launch_r2c_any(const R2CArgs& a_in, int nct, int num_cu, hipStream_t s) {
   R2CArgs a = a_in;
-  if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap16 > 128)
-    return hipErrorNotSupported;
+  if (!any_extents_fit(a.Na, a.Nb) || a.Kap16 > 128) return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
   a.lw = share_waves_log2((a.Na + 31) / 32, a.planes, num_cu);
   const bool pre = a.do_tanh != 0;
@@ -635,8 +634,7 @@ hipError_t launch_r2c_any(const R2CArgs& a_in, int nct, int num_cu, hipStream_t 
 
 hipError_t launch_c2r_any(const C2RArgs& a_in, int nct, int num_cu, hipStream_t s) {
   C2RArgs a = a_in;
-  if (a.Nb < 8 || (int64_t)a.Na * a.Nb * 2 >= (PLANE_OOB >> 1) || a.Kap > 128)
-    return hipErrorNotSupported;
+  if (!any_extents_fit(a.Na, a.Nb) || a.Kap > 128) return hipErrorNotSupported;
   const int nk = any_nk(a.Nb);
   a.lw = share_waves_log2((a.Na + 31) / 32, a.planes, num_cu);
   while (a.lw < 3 && any_c2r_lds(nct, nk, a.lw, a.Kap, a.epilogue != 0) > 160 * 1024) ++a.lw;

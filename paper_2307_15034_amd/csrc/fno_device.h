@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "fno_internal.h"
+#include "fno_routes.h"
 
 namespace fno {
 
@@ -495,12 +496,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void* base, i
 // Rows of an odd length start at any multiple of two bytes.  16-byte buffer
 // accesses work at that alignment (reads of 241-element rows run at 4.2 TB/s
 // against 6.3 TB/s for 256-element ones); the resource starts at the aligned
-// address below the plane and the rest goes into the offset.  Every access
-// lies wholly inside the plane or carries PLANE_OOB (loads read zero, stores
-// are dropped), so no access depends on the range check at the plane's end.
+// address below the plane and the rest goes into the offset.  Columns past the
+// row carry PLANE_OOB.  Rows past the plane, and the last piece of a spectrum
+// whose length is not a multiple of 16 bytes, rely on the range check of the raw
+// buffer resource, which is made for each dword: what lies inside is read or
+// written, the rest reads zero or is dropped.
 // ---------------------------------------------------------------------------
-constexpr int PLANE_OOB = 0x40000000;
-
 struct PlaneRef {
   __amdgpu_buffer_rsrc_t rs;
   int off;

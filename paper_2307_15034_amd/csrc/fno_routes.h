@@ -25,6 +25,17 @@ constexpr int share_waves_log2(int64_t blocks, int64_t planes, int num_cu) {
   return lw;
 }
 
+// Buffer offsets of this value lie past every plane: loads there read zero,
+// stores are dropped.
+constexpr int PLANE_OOB = 0x40000000;
+
+// fp16 planes whose byte offsets, to the end of the last block of 256 rows and
+// with PLANE_OOB added for columns past the row, stay below 2^31 (planes of up to
+// 2^30 bytes).
+constexpr bool any_extents_fit(int64_t Na, int64_t Nb) {
+  return Nb >= 8 && (Na + 255) / 256 * 256 * Nb * 2 < PLANE_OOB;
+}
+
 // A call of few small planes, where the kernels' start-up is most of their
 // time: the generic kernels, a work-group per plane, are quicker there than the
 // ones for any extents, whose work-groups stage tables and whose waves take

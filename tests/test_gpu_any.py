@@ -68,3 +68,59 @@ def test_any_nonfinite_stays_in_its_plane(n):
     assert np.argwhere(~np.isfinite(gx)).tolist() == [[1, 0, 0, 0], [1, 0, n[0] - 1, n[1] - 1]]
     y, _, _ = U.run_all(U.make_layer(n, m, 4, 1, 1, "fp16"), x, w, gy)
     assert np.isfinite(y[[0, 2]]).all() and not np.isfinite(y[[1, 3]]).any()
+
+
+def test_any_planes_of_more_than_half_a_gibibyte():
+    """Offsets past 2^29 bytes, an odd mode count and a row length that the
+    radix-2 kernels do not take: the spectrum against float64 products over the
+    whole plane, the inverse and its tanh' epilogue on sampled rows."""
+    n, m = (16640, 16512), (3, 18)  # 549 MB a plane
+    U.say(f"any large plane: n={n} modes={m}")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((1, 1) + n, device="cuda", generator=g).half()
+    for j in range(2):  # low modes well above the rounding of the stored spectrum
+        ph = 2 * np.pi / n[j] * torch.arange(n[j], device="cuda", dtype=torch.float64)
+        x += (torch.cos(ph) + torch.sin(2 * ph)).half().reshape((-1, 1) if j == 0 else (-1,))
+    gy = torch.randn((1, 1) + n, device="cuda", generator=g).half()
+    w = torch.zeros((1, 1, 2 * m[0], m[1], 2), device="cuda").half()
+    w[..., 0] = 1.0
+    layer = U.make_layer(n, m, 1, 1, 1, "fp16_tanh")
+    xh, gh = layer.spectrum_buffer(0), layer.spectrum_buffer(1)
+    y = layer.fwd(x, w, x_hat=xh)
+    gx = layer.bwd_data(x, w, gy, gy_hat=gh)
+    torch.cuda.synchronize()
+
+    def dft(k, length):
+        p = (k[:, None] * torch.arange(length, device="cuda")) % length
+        return torch.polar(torch.ones((), device="cuda", dtype=torch.float64),
+                           p.double() * (-2 * np.pi / length))
+
+    ka = torch.tensor([0, 1, 2, n[0] - 3, n[0] - 2, n[0] - 1], device="cuda")
+    fa, fb = dft(ka, n[0]), dft(torch.arange(m[1], device="cuda"), n[1])
+
+    def spectrum(v):
+        t = torch.stack([v @ fb.real.T.contiguous(), v @ fb.imag.T.contiguous()])
+        return fa @ torch.complex(t[0], t[1])
+
+    def check(name, got, ref):
+        r = float(torch.linalg.vector_norm(got - ref) / torch.linalg.vector_norm(ref))
+        U.say(f"  {name}: rel_l2 {r:.2e}")
+        assert r <= U.TOL["fp16_tanh"], name
+
+    def stored(h):
+        return torch.view_as_complex(h.view(torch.float16).reshape(2 * m[0], m[1], 2).double())
+
+    check("x_hat", stored(xh), spectrum(torch.tanh(x[0, 0].double())) / (n[0] * n[1]))
+    check("gy_hat", stored(gh), spectrum(gy[0, 0].double()) / (n[0] * n[1]) ** 0.5)
+    rows = torch.tensor([0, 1, 8191, 8192, 12345, n[0] - 2, n[0] - 1], device="cuda")
+    c = torch.tensor([1.0] + [2.0] * (m[1] - 1), device="cuda", dtype=torch.float64)
+
+    def inverse(z):
+        t = fa[:, rows].T.conj() @ (z * c)
+        return (t @ fb.conj()).real
+
+    check("y", y[0, 0, rows].double(), inverse(stored(xh)))
+    dt = 1 - torch.tanh(x[0, 0, rows].double()) ** 2
+    check("gx", gx[0, 0, rows].double(), inverse(stored(gh)) * dt / (n[0] * n[1]) ** 0.5)
+    gyd = gy.cpu().numpy()
+    U.check_routes(layer, x.cpu().numpy(), w.cpu().numpy(), gyd, "r2c_any_kernel", "c2r_any_kernel")

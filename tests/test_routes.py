@@ -77,3 +77,21 @@ def test_few_planes_and_signals(tmp_path):
   expect("144, 60 modes, tanh", few_short_signals({1, 144, 64, true, 256, 256}, true), false);
   expect("8192", few_short_signals({1, 8192, 32, true, 1, 256}, false), false);
   return bad != 0;""")
+
+
+def test_planes_of_any_extents_fit_their_offsets(tmp_path):
+    """Accepted planes: every offset below 2^31 and none of a column past the
+    row inside the plane; refused only where that does not hold for the planes
+    of whole 256-row blocks."""
+    replay(tmp_path, """
+  int bad = 0;
+  for (int64_t na : {2LL, 100LL, 255LL, 256LL, 257LL, 8191LL, 16384LL, 16640LL, 32768LL, 65536LL})
+    for (int64_t nb = 8; nb <= 65536; nb = nb < 64 ? nb + 1 : nb + 121) {
+      const bool fit = any_extents_fit(na, nb);
+      const int64_t rows = (na + 255) / 256 * 256, plane = na * nb * 2;
+      const int64_t last = (rows - 1) * nb * 2 + 15;  // a lane's row, the alignment rest
+      const bool safe = last + PLANE_OOB < (int64_t)1 << 31 && plane <= PLANE_OOB;
+      if ((fit && !safe) || (na % 256 == 0 && fit != (plane < (int64_t)1 << 30)))
+        ++bad, std::printf("%lld x %lld: %d\\n", (long long)na, (long long)nb, fit);
+    }
+  return bad != 0;""")
