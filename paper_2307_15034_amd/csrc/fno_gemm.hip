@@ -1555,7 +1555,8 @@ hipError_t launch_quad(const GemmArgs& a, hipStream_t s) {
   if (!quads_along(g, CL_BT, 0) || !quads_along(g, CL_BT, 1)) return hipErrorNotSupported;
   const int64_t tm = (g.c[CL_M].size + 15) / 16, tn = (g.c[CL_N].size + 15) / 16;
   const int64_t waves = tm * tn * (cb.size / 4);
-  if (waves >= ((int64_t)1 << 31)) return hipErrorNotSupported;
+  if (waves >= ((int64_t)1 << 31) || !quad_pays(g.c[CL_M].size, g.c[CL_N].size, K, waves))
+    return hipErrorNotSupported;
   g.tiles_m = (int)tm;
   g.tiles_n = (int)tn;
   const dim3 grid((unsigned)((waves + 3) / 4)), block(256);

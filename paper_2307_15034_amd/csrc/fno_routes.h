@@ -102,4 +102,18 @@ constexpr bool fast_planes(const PlaneShape& g, bool inverse) {
          (inverse && work <= 12288 && g.planes <= 3 * (int64_t)g.num_cu);
 }
 
+// Pairwise fp16 steps batched over an index t that is innermost in memory, M x N
+// results of K products for each t: whether a wave per 16 x 16 results of four t
+// (`waves` in all) beats the GEMM tiles.  It does without an upper bound, although
+// each wave fetches its rows again (the neighbours' are in the L1): 2048 x 128
+// results of 512 products for 32 t 450 against 1175 us, 2048 x 256 of 128 226
+// against 719, 1024 x 128 of 128 59 against 93, 512 x 64 of 48 13 against 19.  It
+// loses where few waves walk a long reduction, which the tiles split (64 x 64 of
+// 384 for 32 t 29.7 against 26.3 us, 48 x 32 of 384 for 16 22.3 against 17.2), and
+// by 1 to 2 us of start-up where a small step fills half of its 16 columns.
+constexpr bool quad_pays(int64_t M, int64_t N, int64_t K, int64_t waves) {
+  if (waves <= 128 && K > 256) return false;
+  return !(waves <= 256 && M <= 64 && N <= 8 && K <= 32);
+}
+
 }  // namespace fno

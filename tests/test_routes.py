@@ -95,3 +95,24 @@ def test_planes_of_any_extents_fit_their_offsets(tmp_path):
         ++bad, std::printf("%lld x %lld: %d\\n", (long long)na, (long long)nb, fit);
     }
   return bad != 0;""")
+
+
+def test_batched_steps(tmp_path):
+    """Steps on either side of the line as measured (results, products, t)."""
+    replay(tmp_path, """
+  int bad = 0;
+  auto expect = [&](int M, int N, int K, int t, bool want) {
+    const long waves = (long)((M + 15) / 16) * ((N + 15) / 16) * (t / 4);
+    if (quad_pays(M, N, K, waves) != want) ++bad, std::printf("%d %d %d %d\\n", M, N, K, t);
+  };
+  expect(48, 32, 384, 16, false);
+  expect(64, 64, 384, 32, false);
+  expect(32, 4, 8, 192, false);
+  expect(48, 8, 32, 192, false);
+  expect(2048, 128, 512, 32, true);
+  expect(128, 32, 12, 2048, true);
+  expect(256, 128, 384, 12, true);
+  expect(64, 32, 48, 16, true);
+  expect(32, 8, 128, 192, true);
+  expect(512, 8, 48, 32, true);
+  return bad != 0;""")
