@@ -1077,8 +1077,7 @@ __global__ __launch_bounds__(256) void pair_ew_kernel(PairArgs a, int64_t items,
   }
 }
 
-// Four results per thread where the innermost extent allows it and the
-// results still fill the chip; pairs otherwise.
+// NV results per thread (four where that pays, pairs otherwise).
 template <int NV>
 void launch_ew(const PairArgs& a, hipStream_t s) {
   const int64_t items = a.out_size / NV;
@@ -1438,7 +1437,7 @@ hipError_t launch_pair(const PairArgs& a_in, hipStream_t s) {
   const bool ew = a.red_size == 1 && a.n_out > 0 && a.out_size <= 0x7fffffffll * 256 &&
                   a.out_ext[a.n_out - 1] % 2 == 0;
   if (ew && a.out_ext[a.n_out - 1] % 4 == 0 && ((uintptr_t)a.out & 15u) == 0 &&
-      a.out_size >= (int64_t)4 * 64 * 1024) {
+      four_products_pay(a.out_size, a.a_stride_out[a.n_out - 1], a.b_stride_out[a.n_out - 1])) {
     launch_ew<4>(a, s);
   } else if (ew) {
     launch_ew<2>(a, s);

@@ -116,4 +116,15 @@ constexpr bool quad_pays(int64_t M, int64_t N, int64_t K, int64_t waves) {
   return !(waves <= 256 && M <= 64 && N <= 8 && K <= 32);
 }
 
+// Elementwise and outer products of `results` values: four results per thread
+// instead of two.  Only outer products gain, whose operand without the innermost
+// index (stride other than one) is loaded once for the four, and only from about
+// 1.25 million results on, where fewer threads still fill the chip (0.79 M 4.8
+// against 4.4 us, 1.57 M 5.9 against 6.5, 16.8 M 25.0 against 33.9, fp16); where
+// both operands stream, two are as quick or quicker at any size (2.1 M 9.2 against
+// 7.3 us, 33.6 M 67.2 against 64.5).
+constexpr bool four_products_pay(int64_t results, int64_t a_stride, int64_t b_stride) {
+  return results >= (int64_t)5 << 18 && (a_stride != 1 || b_stride != 1);
+}
+
 }  // namespace fno

@@ -116,3 +116,13 @@ def test_batched_steps(tmp_path):
   expect(32, 8, 128, 192, true);
   expect(512, 8, 48, 32, true);
   return bad != 0;""")
+
+
+def test_products_per_thread(tmp_path):
+    replay(tmp_path, """
+  int bad = 0;
+  bad += four_products_pay(262144, 1, 0) || four_products_pay(786432, 1, 0);
+  bad += !four_products_pay(1572864, 1, 0) || !four_products_pay(16777216, 0, 1);
+  bad += !four_products_pay(8388608, 1, 8);
+  bad += four_products_pay(2097152, 1, 1) || four_products_pay(33554432, 1, 1);
+  return bad;""")
