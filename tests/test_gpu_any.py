@@ -16,9 +16,9 @@ if torch.cuda.is_available():
 
 CASES = [
     # (n, modes, B, Cin, Cout)
-    ((5, 8), (2, 3), 30, 30, 20),       # one piece per row, eight planes per work-group
-    ((33, 9), (3, 5), 20, 20, 15),      # second row block holds one row; Nyquist-free odd rows
-    ((64, 63), (17, 7), 2, 3, 3),       # two waves per plane, 34 leading slots
+    ((5, 12), (2, 3), 60, 20, 18),      # two pieces per row, eight planes per work-group
+    ((33, 9), (3, 5), 40, 20, 20),      # second row block holds one row; Nyquist-free odd rows
+    ((64, 63), (17, 7), 26, 20, 20),    # two waves per plane, 34 leading slots
     ((65, 65), (8, 33), 1, 4, 3),       # second segment holds one column, four mode tiles
     ((127, 129), (24, 17), 3, 3, 4),    # four waves, 48 leading slots (three tiles)
     ((129, 127), (40, 21), 1, 3, 3),    # eight waves, 80 leading slots (five tiles)
@@ -28,8 +28,8 @@ CASES = [
     ((700, 44), (64, 22), 1, 2, 2),     # three chunks, tables too large for LDS
     ((20, 1001), (5, 6), 2, 3, 3),      # eight segments, the last of 105 columns
     ((241, 241), (20, 20), 3, 60, 50),  # more planes than work-groups
-    ((31, 40), (9, 11), 9, 120, 50),    # one wave per plane, several planes per wave
-    ((7, 21, 35), (2, 5, 9), 2, 3, 3),  # 3-D
+    ((31, 41), (9, 11), 18, 120, 60),   # one wave per plane, several planes per wave
+    ((7, 21, 35), (2, 5, 9), 10, 12, 12),  # 3-D
 ]
 
 
@@ -47,9 +47,10 @@ def test_any_parity(case, mode):
     rgw = O.bwd_weight(x, gy, n, m, mode)
     for name, a, b in (("y", y, ry), ("gx", gx, rgx), ("gW", U.cplx(gw), rgw)):
         assert U.rel(a, b) <= U.TOL[mode], (name, U.rel(a, b))
+    U.check_routes(layer, x, w, gy, "r2c_any_kernel", "c2r_any_kernel")
 
 
-@pytest.mark.parametrize("n", [(9, 13), (130, 137)])
+@pytest.mark.parametrize("n", [(65, 81), (130, 137)])
 def test_any_nonfinite_stays_in_its_plane(n):
     """NaN and inf in one plane (its first and last samples share 16-byte
     pieces and 4-byte words with the neighbouring planes) leave the others
@@ -64,6 +65,7 @@ def test_any_nonfinite_stays_in_its_plane(n):
     gy = rng.standard_normal((4, 1) + n).astype(np.float16)
     layer = U.make_layer(n, m, 4, 1, 1, "fp16_tanh")
     y, gx, _ = U.run_all(layer, x, w, gy)
+    U.check_routes(layer, x, w, gy, "r2c_any_kernel", "c2r_any_kernel")
     assert np.isnan(y[1]).all() and np.isfinite(y[[0, 2, 3]]).all()
     assert np.argwhere(~np.isfinite(gx)).tolist() == [[1, 0, 0, 0], [1, 0, n[0] - 1, n[1] - 1]]
     y, _, _ = U.run_all(U.make_layer(n, m, 4, 1, 1, "fp16"), x, w, gy)

@@ -15,19 +15,19 @@ if torch.cuda.is_available():
 
 CASES = [
     # (n, modes, B, Cin, Cout)
-    ((5, 8), (2, 3), 30, 30, 20),       # odd rows, one piece
-    ((6, 9), (3, 5), 20, 20, 15),       # folded rows, odd columns, a wave per plane
+    ((5, 8), (2, 3), 40, 30, 28),       # odd rows, one piece
+    ((6, 9), (3, 5), 60, 20, 18),       # folded rows, odd columns, a wave per plane
     ((34, 38), (17, 18), 20, 20, 15),   # both folded: 17 row pairs, 19 columns a half
-    ((33, 130), (8, 33), 1, 3, 2),      # second segment of a half holds one column
-    ((64, 66), (32, 34), 2, 3, 2),      # every mode retained, four mode tiles
+    ((33, 130), (8, 33), 9, 30, 29),    # second segment of a half holds one column
+    ((64, 66), (32, 34), 10, 26, 26),   # every mode retained, four mode tiles
     ((70, 33), (24, 17), 2, 3, 3),      # 24 slots a class (two tiles of 16)
     ((257, 64), (6, 20), 1, 2, 2),      # second chunk holds one row
     ((600, 131), (64, 64), 1, 2, 2),    # folded rows over two chunks, 128 slots
     ((1030, 40), (5, 6), 1, 3, 3),      # few planes: five parts
     ((512, 512), (21, 35), 1, 3, 2),    # two parts, folded, 64-mode tiles
     ((128, 128), (32, 32), 2, 20, 17),
-    ((20, 24), (4, 5), 9, 120, 40),     # several planes per wave
-    ((7, 20, 36), (2, 5, 18), 2, 3, 2),  # 3-D
+    ((20, 24), (4, 5), 18, 120, 58),    # several planes per wave
+    ((7, 20, 36), (2, 5, 18), 10, 15, 15),  # 3-D
 ]
 
 
@@ -45,15 +45,18 @@ def test_any32_parity(case, mode):
                        ("gW", U.cplx(gw), O.bwd_weight(x, gy, n, m, mode))):
         # 32-bit sums of a few hundred terms: well inside the gate of 1e-5
         assert U.rel(a, b) <= 2e-6, (name, U.rel(a, b))
+    U.check_routes(layer, x, w, gy, "r2c_any32_kernel", "c2r_any32_kernel")
 
 
 def test_any32_nonfinite_stays_in_its_plane():
-    n, m = (9, 13), (3, 5)
+    n, m = (130, 137), (3, 5)
     rng = np.random.default_rng(5)
     x = rng.standard_normal((3, 1) + n).astype(np.float32)
     x[1, 0, 0, 0] = x[1, 0, -1, -1] = np.nan
     w = np.zeros((1, 1, 2 * m[0], m[1], 2), np.float32)
     w[..., 0] = 1.0
     layer = U.make_layer(n, m, 3, 1, 1, "fp32")
-    y, _, _ = U.run_all(layer, x, w, rng.standard_normal((3, 1) + n).astype(np.float32))
+    gy = rng.standard_normal((3, 1) + n).astype(np.float32)
+    y, _, _ = U.run_all(layer, x, w, gy)
+    U.check_routes(layer, x, w, gy, "r2c_any32_kernel", "c2r_any32_kernel")
     assert np.isnan(y[1]).all() and np.isfinite(y[[0, 2]]).all()

@@ -62,3 +62,55 @@ def test_cp_steps(case, prec, policy):
         e = U.rel(got, ref)
         U.say(f"  {name}: rel_l2 = {e:.3e} (tol {U.TOL[prec]:.0e})")
         assert np.isfinite(e) and e <= U.TOL[prec], name
+
+
+TUCKER = [
+    # (n, modes, B, Cin, Cout, ranks, a kernel that a call of it runs: its names)
+    # 12 contracted elements of 64 rows: the last quad of a stage lies past them
+    ((32, 32), (8, 12), 4, 36, 64, (8, 12, 5, 3), ("pair_gemm_kernel<64, 64, 2, true, true, 16>",)),
+    ((32, 32), (8, 12), 5, 36, 64, (20, 24, 4, 4), ("pair_quad_kernel<32>",)),
+    # outer products of more than 1.3 million results: four per thread
+    ((64, 64), (32, 32), 2, 128, 128, (13, 13, 6, 3),
+     ("pair_ew_kernel<4", "pair_ew_kernelILi4")),
+]
+
+
+@pytest.mark.parametrize("policy", ["min_result", "min_net"])
+@pytest.mark.parametrize("prec", ["fp32", "fp16_tanh"])
+@pytest.mark.parametrize("case", range(len(TUCKER)))
+def test_tucker_steps(case, prec, policy):
+    n, modes, bt, ci, co, rank, kernel = TUCKER[case]
+    _, npdt, oprec = U.prec_codes(prec)
+    U.say(f"tucker steps {case}: n={n} modes={modes} B={bt} C={ci}->{co} R={rank} {prec} {policy}")
+    rng = np.random.default_rng(np.random.SeedSequence([4100 + case]))
+    kd = (2 * modes[0], modes[1])
+
+    def cpx(shape):
+        return (rng.standard_normal(tuple(shape) + (2,)) * 0.3).astype(npdt)
+
+    w = {"core": cpx(rank), "u_in": cpx((ci, rank[0])), "u_out": cpx((co, rank[1])),
+         "u_mode": [cpx((k, r)) for k, r in zip(kd, rank[2:])]}
+    x = rng.standard_normal((bt, ci) + n).astype(npdt)
+    gy = rng.standard_normal((bt, co) + n).astype(npdt)
+    layer = U.make_layer(n, modes, bt, ci, co, prec, policy=0 if policy == "min_result" else 1,
+                         tucker_rank=rank)
+    y, gx, gw = U.run_all(layer, x, w, gy)
+    args = (U.cplx(w["core"]), U.cplx(w["u_in"]), U.cplx(w["u_out"]),
+            [U.cplx(u) for u in w["u_mode"]])
+    g_core, g_in, g_out, g_mode = O.tucker_bwd_weight(x, gy, *args, n, modes, oprec)
+    gwc = U.gw_complex(gw)
+    pairs = [("y", y, O.tucker_fwd(x, *args, n, modes, oprec, policy)),
+             ("gx", gx, O.tucker_bwd_data(x, *args, gy, n, modes, oprec, policy)),
+             ("g_core", gwc["core"], g_core), ("g_u_in", gwc["u_in"], g_in),
+             ("g_u_out", gwc["u_out"], g_out)]
+    pairs += [(f"g_u_mode{j}", gwc["u_mode"][j], g_mode[j]) for j in range(2)]
+    for name, got, ref in pairs:
+        e = U.rel(got, ref)
+        U.say(f"  {name}: rel_l2 = {e:.3e} (tol {U.TOL[prec]:.0e})")
+        assert np.isfinite(e) and e <= U.TOL[prec], name
+    if prec == "fp16_tanh" and policy == "min_result":
+        xd, gyd = U.dev(x), U.dev(gy)
+        wd = {k: [U.dev(u) for u in v] if isinstance(v, list) else U.dev(v) for k, v in w.items()}
+        names = U.kernels(lambda: (layer.fwd(xd, wd), layer.bwd(xd, wd, gyd)))
+        U.say(" ".join(names))
+        assert not names or any(q in k for k in names for q in kernel), names

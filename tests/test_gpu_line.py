@@ -15,9 +15,9 @@ if torch.cuda.is_available():
 
 CASES = [
     # (N, modes, B, Cin, Cout)
-    (8, 3, 2, 3, 2),           # one 16-byte piece
-    (9, 5, 2, 2, 3),           # every second signal starts off a 4-byte address
-    (127, 64, 1, 2, 2),        # one partial row, four mode tiles, all modes
+    (8, 3, 60, 20, 18),        # one 16-byte piece
+    (9, 5, 60, 20, 18),        # every second signal starts off a 4-byte address
+    (127, 64, 30, 18, 18),     # one partial row, four mode tiles, all modes
     (257, 17, 3, 5, 7),        # third row holds one sample
     (1000, 1, 2, 17, 18),      # more than one 16-signal tile, one mode
     (4096, 32, 2, 9, 9),       # exactly one block
@@ -42,6 +42,7 @@ def test_line_parity(case, mode):
     rgw = O.bwd_weight(x, gy, (n,), (m,), mode)
     for name, a, b in (("y", y, ry), ("gx", gx, rgx), ("gW", U.cplx(gw), rgw)):
         assert U.rel(a, b) <= U.TOL[mode], (name, U.rel(a, b))
+    U.check_routes(layer, x, w, gy, "r2c_line_kernel", "c2r_line_kernel")
 
 
 def test_line_nonfinite_stays_in_its_signal():

@@ -38,6 +38,8 @@ def test_parts_parity(case):
                        ("gx", gx, O.bwd_data(x, wc, gy, n, m, "fp16_tanh")),
                        ("gW", U.cplx(gw), O.bwd_weight(x, gy, n, m, "fp16_tanh"))):
         assert U.rel(a, b) <= U.TOL["fp16_tanh"], (name, U.rel(a, b))
+    names = U.kernels(lambda: layer.fwd(U.dev(x), U.dev(w)))
+    assert not names or any("part_sum_kernel" in k for k in names), names
     # the combined backward, with and without the cached spectrum
     xd, wd, gyd = U.dev(x), U.dev(w), U.dev(gy)
     xh = layer.spectrum_buffer(0)
