@@ -1,24 +1,28 @@
 // Truncated transforms of fp32 planes of any extents (Nb >= 8, up to 64
 // last-axis and 128 leading-axis modes), v_mfma_f32_16x16x4_f32.
 //
-// The fp32 products are bound by the matrix cores (157 TFLOP/s; a 128 x 128
-// transform with 32 x 32 modes as plain DFT products needs 55 us of them for
-// 2048 planes against 33 us of memory traffic), so an even axis is folded
-// first: e^{-2 pi i k (n + N/2) / N} = (-1)^k e^{-2 pi i k n / N}, so even
+// As plain DFT products the fp32 transforms would be bound by the matrix cores
+// (157 TFLOP/s: 128 x 128 with 32 x 32 modes, 2048 planes, 55 us of them against
+// 33 us of memory traffic), so an even axis is folded first:
+// e^{-2 pi i k (n + N/2) / N} = (-1)^k e^{-2 pi i k n / N}, so even
 // frequencies need only u[n] + u[n + N/2] and odd ones only their difference,
 // over half the length (radix 2, in fp32).  FB folds the last axis (modes
 // in the order even, odd), FA the leading one: a wave's two row tiles are then
 // rows r and r + Na/2.  Odd axes are taken whole.
 //
 // As in the fp16 kernels for any extents, the last axis goes in segments of 64
-// (32 with more than 32 modes) columns of one table held in LDS, the accumulators (in the inverse the
-// rows of V) rotated in fp32 between segments; 1 to 8 waves share a plane,
-// and a plane's rows are shared by several work-groups where planes are few.
-// A wave's next segment is in flight while one is multiplied.
+// (32 with more than 32 modes) columns of one table held in LDS, the accumulators
+// (in the inverse the rows of V) rotated in fp32 between segments; 1 to 8 waves
+// share a plane, and a plane's rows are shared by several work-groups where
+// planes are few.  A wave's next segment is in flight while one is multiplied.
 //
-// 2048 planes of 128 x 128, 32 x 32 modes: forward 130 -> 72 us, inverse 125 ->
-// 65 us against the generic kernels (tables from L2, no radix 2, nothing in
+// 2048 planes of 128 x 128, 32 x 32 modes: forward 130 -> 70 us, inverse 125 ->
+// 64 us against the generic kernels (tables from L2, no radix 2, nothing in
 // flight); 32 planes of 512 x 512, 42 x 35 modes: 478 -> 57 and 436 -> 57 us.
+// Folded, neither limit is reached alone: the matrix cores are busy 36 and 37% of
+// the time (61 and 67 TFLOP/s) at 2.4 and 3.0 TB/s, and the waves wait for a
+// quarter and two fifths of theirs: the two steps of a plane follow one another,
+// with one work-group on a compute unit.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

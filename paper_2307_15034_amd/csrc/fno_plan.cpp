@@ -1340,7 +1340,8 @@ fno_status run_r2c(const Plan* pl, const void* in, void* spec, void* inter, int6
     else if (e != hipErrorNotSupported) return hip_fail(e, kname);
   }
   if (!done && g.elem == ELEM_F16 && g.nd >= 2 && !few_small_planes(plane_shape(pl, a.planes), false)) {
-    // every other plane (all but the widest mode counts and the shortest rows)
+    // every other plane (all but the widest mode counts, the shortest rows and
+    // few small planes)
     share(false);
     R2CArgs b = a;
     b.twS = pl->t.sgF;
