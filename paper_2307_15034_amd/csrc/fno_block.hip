@@ -111,50 +111,73 @@ __device__ __forceinline__ void store_row8(_Float16* row, int64_t p, int64_t P, 
   }
 }
 
-// W [rows][cols] (16-byte aligned, at most 128 x 128) into LDS rows of stride
-// ld (zero up to the tile's NR rows and Kp columns), transposed with TR: 16
-// lanes take a row's 16-byte pieces and every load of a thread is in flight
-// before the first is used (element by element, each waited for, a work-group's
-// start took 20 us longer at 128 x 128; 8 x 64 channels of 256 x 256 points,
-// forward 84 -> 75 us).
-template <int NR, bool TR>
-__device__ __forceinline__ void stage_skip(_Float16* WS, int ld, int Kp, const _Float16* w, int N,
-                                           int K) {
-  const int rows = TR ? K : N, cols = TR ? N : K;
-  const int c8 = (threadIdx.x & 15) * 8, r0 = threadIdx.x >> 4;
-  constexpr int RI = TR ? 8 : (NR + 15) / 16;  // row visits of a thread
-  h8 v[RI];
-#pragma unroll
-  for (int i = 0; i < RI; ++i) {
-    const int r = r0 + 16 * i;
-    v[i] = MM<_Float16>::zero();
-    if (r < rows && c8 + 8 <= cols && cols % 8 == 0) {
-      v[i] = *reinterpret_cast<const h8*>(w + r * cols + c8);
-    } else if (r < rows) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (c8 + e < cols) v[i][e] = w[r * cols + c8 + e];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < RI; ++i) {
-    const int r = r0 + 16 * i;
-    if (TR) {
-      if (r < Kp) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (c8 + e < NR) WS[(c8 + e) * ld + r] = v[i][e];
-      }
-    } else if (r < NR && c8 < Kp) {
-      *reinterpret_cast<h8*>(WS + r * ld + c8) = v[i];
-    }
-  }
-}
-
 // n halves of LDS (a multiple of 8, 16-byte aligned) to zero, by NT threads.
 template <int NT>
 __device__ __forceinline__ void clear_lds(_Float16* p, int n) {
   for (int i = threadIdx.x; i < n / 8; i += NT) reinterpret_cast<u32x4*>(p)[i] = u32x4{0u, 0u, 0u, 0u};
+}
+
+// W [rows][cols] (16-byte aligned, at most 128 x 128) into LDS rows of stride
+// ld (zero up to the tile's NR rows and Kp columns), transposed with TR, every
+// load of a thread in flight before the first is used (element by element, each
+// waited for, a work-group's start took 20 us longer at 128 x 128; 8 x 64
+// channels of 256 x 256 points, forward 84 -> 75 us).  Rows of a multiple of
+// eight: 16 lanes take a row's 16-byte pieces.  Others: W is read as one run of
+// pieces, each put down element by element (12 samples of 248 points, 20 to 128
+// channels, data gradient: 11.2 us by pieces of rows with a lane in five at work,
+// 4.8 so).
+template <int NR, bool TR>
+__device__ __forceinline__ void stage_skip(_Float16* WS, int ld, int Kp, const _Float16* w, int N,
+                                           int K) {
+  const int rows = TR ? K : N, cols = TR ? N : K;
+  if (cols % 8 == 0) {
+    const int c8 = (threadIdx.x & 15) * 8, r0 = threadIdx.x >> 4;
+    constexpr int RI = TR ? 8 : (NR + 15) / 16;  // row visits of a thread
+    h8 v[RI];
+#pragma unroll
+    for (int i = 0; i < RI; ++i) {
+      const int r = r0 + 16 * i;
+      v[i] = MM<_Float16>::zero();
+      if (r < rows && c8 < cols) v[i] = *reinterpret_cast<const h8*>(w + r * cols + c8);
+    }
+#pragma unroll
+    for (int i = 0; i < RI; ++i) {
+      const int r = r0 + 16 * i;
+      if (TR) {
+        if (r < Kp) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (c8 + e < NR) WS[(c8 + e) * ld + r] = v[i][e];
+        }
+      } else if (r < NR && c8 < Kp) {
+        *reinterpret_cast<h8*>(WS + r * ld + c8) = v[i];
+      }
+    }
+    return;
+  }
+  constexpr int PI = 8;  // pieces of a thread: 128 x 128 / 8 / 256
+  const int n = rows * cols, np = n / 8;
+  h8 v[PI];
+#pragma unroll
+  for (int i = 0; i < PI; ++i)
+    if (256 * i < np)
+      v[i] = *reinterpret_cast<const h8*>(w + 8 * min((int)threadIdx.x + 256 * i, np - 1));
+  clear_lds<256>(WS, NR * ld);
+  __syncthreads();
+  const auto put = [&](int r, int c, _Float16 x) { WS[TR ? c * ld + r : r * ld + c] = x; };
+#pragma unroll
+  for (int i = 0; i < PI; ++i) {
+    const int q = threadIdx.x + 256 * i;
+    if (q >= np) break;
+    int r = 8 * q / cols, c = 8 * q - r * cols;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      put(r, c, v[i][e]);
+      if (++c == cols) c = 0, ++r;
+    }
+  }
+  const int last = 8 * np + threadIdx.x;  // the last partial piece
+  if (last < n) put(last / cols, last % cols, w[last]);
 }
 
 struct EpiMixArgs {

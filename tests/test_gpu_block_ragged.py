@@ -24,6 +24,12 @@ CASES = [
     (129, 3, 33, 64, False),   # odd channel counts, two output tiles per wave
     (1225, 4, 128, 128, True),
     (4097, 2, 64, 64, True),
+    # skip weights whose rows are not a multiple of eight, aligned points
+    (248, 12, 20, 128, False),  # pieces run over rows, 320 of them
+    (64, 2, 1, 1, True),        # less than one piece
+    (72, 3, 3, 5, False),       # one piece and seven values
+    (128, 2, 127, 127, True),   # 16129 values: eight pieces a thread
+    (128, 2, 121, 8, False),    # one direction by rows, the other by runs
 ]
 
 
