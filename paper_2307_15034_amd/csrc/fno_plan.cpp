@@ -2191,23 +2191,29 @@ SideStream* side_stream_of_device(hipStream_t s) {
   return &(g_side[dev] = ss);
 }
 
+FactorShape factor_shape(const fno_conv_desc* d, const Plan* pl) {
+  const Geo& g = pl->g;
+  const bool cp = d->weight_kind == FNO_WEIGHT_CP;
+  const int64_t r0 = d->rank[0], r1 = cp ? r0 : d->rank[1];
+  FactorShape f{};
+  f.cp = cp;
+  f.fp16 = g.elem == ELEM_F16;
+  f.generic = g.act == ACT_SIGMA || g.Nb < 8 || (g.nd == 1 ? !f.fp16 : g.Kb > 64);
+  f.ndim = g.nd;
+  f.points = g.B * (g.Cin + g.Cout) * g.N;
+  f.Nb = g.Nb;
+  f.Kbp = g.Kbp;
+  f.products = g.B * g.K * (g.Cin * r0 + g.Cout * r1);
+  f.weight = cp ? 0 : g.K * r0 * r1;
+  return f;
+}
+
 // The side stream for a call of `d`, or null (the caller then runs both parts
 // on its own stream), also where the fork would cost more than the overlap
-// gives.  Two streams and their events take 130 to 150 us of host time a step,
-// so a step launched from the host has to be long: Tucker weights with
-// B max(Cin, Cout) N of 13.8 M points 300 to 350 us forked, 278 on one stream;
-// 33 M 290 to 350 against 322; 67 M 336 to 369 against 398; 134 M 594 against
-// 704.  CP weights have little beside the transforms: 270 to 320 against 242
-// at 33 M, 785 against 753 at 67 M, 711 against 701 at 134 M.  Recorded into a
-// graph the fork costs the device alone: 0.5 M points 149 to 189 us forked and
-// 106 to 165 on one stream, 17 M 262 and 288, 134 M (CP) 672 and 704.
-SideStream* side_stream_locked(const fno_conv_desc* d, hipStream_t s) {
+// gives (fork_pays).
+SideStream* side_stream_locked(const fno_conv_desc* d, const Plan* pl, ForkCall call, hipStream_t s) {
   SideStream* ss = side_stream_of_device(s);
-  if (!ss) return nullptr;
-  const int64_t points = d->batch * std::max<int64_t>(d->c_in, d->c_out) * nspatial(d);
-  const bool pays = capturing(s) ? points >= (int64_t)1 << 23
-                                 : d->weight_kind != FNO_WEIGHT_CP && points >= (int64_t)1 << 25;
-  return pays ? ss : nullptr;
+  return ss && fork_pays(factor_shape(d, pl), call, capturing(s)) ? ss : nullptr;
 }
 
 // Two branches after the work already on `s`: on the caller's stream
@@ -2221,9 +2227,10 @@ SideStream* side_stream_locked(const fno_conv_desc* d, hipStream_t s) {
 // from the host one by one, its few large kernels start while the side's
 // many small ones are still being enqueued.
 template <typename FA, typename F1, typename FB, typename F2>
-fno_status run_forked(const fno_conv_desc* d, hipStream_t s, FA side_a, F1 first, FB side_b, F2 second) {
+fno_status run_forked(const fno_conv_desc* d, const Plan* pl, hipStream_t s, FA side_a, F1 first,
+                      FB side_b, F2 second) {
   std::unique_lock<std::mutex> lk(g_side_mutex);
-  SideStream* ss = side_stream_locked(d, s);
+  SideStream* ss = side_stream_locked(d, pl, FORK_BACKWARD, s);
   fno_status st;
   if (!ss) {
     lk.unlock();
@@ -2281,7 +2288,7 @@ fno_status run_path_forked(const fno_conv_desc* d, const Plan* pl, bool adjoint,
   SideStream* ss = nullptr;
   if (allow_side && path_has_weight_steps(path, 4 + (size_t)d->ndim)) {
     lk.lock();
-    ss = side_stream_locked(d, s);
+    ss = side_stream_locked(d, pl, FORK_PATH, s);
     if (!ss) lk.unlock();
   }
   hipError_t e = ss ? hipEventRecord(ss->fork, s) : hipSuccess;
@@ -2590,7 +2597,7 @@ fno_status fno_spectral_conv_bwd_weight(const fno_conv_desc* d, const void* x, c
   }
   // the chains after P and Q on the side streams when they exist
   std::unique_lock<std::mutex> lk(g_side_mutex);
-  SideStream* ss = capturing(s) ? nullptr : side_stream_locked(d, s);
+  SideStream* ss = capturing(s) ? nullptr : side_stream_locked(d, pl, FORK_WGRAD, s);
   WgradBranches wb{};
   if (ss) wb = ss->branches();
   const WgradBranches* b = ss ? &wb : nullptr;
@@ -2698,7 +2705,7 @@ fno_status fno_spectral_conv_bwd(const fno_conv_desc* d, const void* x, const fn
       const float sc = (float)(1.0 / std::sqrt((double)g.N));
       return run_c2r(pl, gxs, gx, inter, g.Cin, sc, pre_on ? x : nullptr, s, bounds);
     };
-    return run_forked(d, s, side_a, spectra, side_b, data_part);
+    return run_forked(d, pl, s, side_a, spectra, side_b, data_part);
   }
   // dense: the data part's regions inside wsd, laid out as in bwd_data (its
   // first region, the gradient spectrum, is unused: gh holds it)

@@ -127,4 +127,48 @@ constexpr bool four_products_pay(int64_t results, int64_t a_stride, int64_t b_st
   return results >= (int64_t)5 << 18 && (a_stride != 1 || b_stride != 1);
 }
 
+// A call with factorised weights, as far as its time goes.
+struct FactorShape {
+  bool cp, fp16;
+  bool generic;      // its transforms run in the generic kernels
+  int ndim;
+  int64_t points;    // B (Cin + Cout) N
+  int Nb, Kbp;       // last axis: points, padded modes
+  int64_t products;  // with u_in and u_out: B modes (Cin r_in + Cout r_out)
+  int64_t weight;    // Tucker: modes r_in r_out
+};
+
+// What its transforms (a forward's) and the products of its weight gradient take
+// beyond their launches, in us: 2.5 TB/s with ramps; the generic kernels by the
+// products, a 1-D signal walked by one work-group.
+constexpr double factor_transforms_us(const FactorShape& f) {
+  if (!f.generic) return 0.4e-6 * (double)f.points * (f.fp16 ? 2 : 4);
+  return 10e-8 * (double)f.points * f.Kbp + (f.ndim == 1 ? 4e-3 * f.Nb * f.Kbp : 0.0);
+}
+constexpr double factor_products_us(const FactorShape& f) {
+  return 35e-8 * (double)f.products + 107e-6 * (double)f.weight;
+}
+
+// Whether a call gains from its side streams.  path: the steps of the weight alone
+// beside the transforms; backward: the weight gradient too; wgrad: its own chains.
+// Two streams and their events take 130 to 150 us of host time in a backward
+// launched from the host, so what they run beside has to be long; recorded into a
+// graph they cost the device's dependencies alone.  Measured both ways over 613
+// shapes of 0.1 to 260 M points, the lines give the quicker way to within (mean, calls
+// more than 5% off; in brackets with one line on the points for all):
+//   launched  path and backward 0.8%, 71 of 1226 (1.3%, 114), wgrad 0.2%, 9 of 613 (2.0%, 53)
+//   recorded  path 0.9%, 42 of 613 (1.1%, 57), backward 0.7%, 34 of 613 (2.7%, 104)
+// In us, forked and on one stream: Tucker, one sample of 12 to 26 channels, 114 x 216,
+// 22 x 91 modes, backward recorded 163 and 229; 2 of 14 to 25, 125 x 390, 40 x 128
+// modes, backward launched 393 and 455; CP of rank 16, 32 samples of 64 channels, 128 x
+// 128, 64 x 32 modes, backward launched 212 and 170, recorded 155 and 167.
+enum ForkCall { FORK_PATH, FORK_BACKWARD, FORK_WGRAD };
+constexpr bool fork_pays(const FactorShape& f, ForkCall call, bool recorded) {
+  if (call == FORK_WGRAD) return !recorded && factor_products_us(f) >= 65;
+  const double us = factor_transforms_us(f);
+  if (recorded) return us >= (call == FORK_BACKWARD ? (f.cp ? 6 : 2) : (f.cp ? 60 : 8));
+  if (f.cp) return us >= 100;
+  return us + (call == FORK_BACKWARD ? 10 * f.ndim : 0) >= 55;  // (weight steps by axis)
+}
+
 }  // namespace fno

@@ -86,6 +86,11 @@ def test_graph_replay_matches_eager(prec):
 # ranks): Tucker ranks (r_in, r_out, r_1, r_2), CP rank (R,).
 FACTOR_CASES = {"tucker": ((32, 32), (8, 8), 4, 32, 24, (8, 6, 4, 4)),
                 "cp": ((32, 32), (8, 8), 4, 32, 24, (12,))}
+# Transforms long enough (the generic kernels of 70 modes) that the recorded forward of
+# Tucker weights and both kinds' backward fork to the side streams, while the eager
+# calls keep to one.
+FORKED_CASES = {"tucker": ((8, 160), (3, 70), 10, 26, 24, (8, 6, 3, 5)),
+                "cp": ((8, 160), (3, 70), 10, 26, 24, (12,))}
 
 
 def _factor_weights(rng, kind, ci, co, kd, rank, npdt):
@@ -106,13 +111,14 @@ def _flat(t):
     return [t]
 
 
+@pytest.mark.parametrize("forked", [False, True])
 @pytest.mark.parametrize("separate", [False, True])
 @pytest.mark.parametrize("policy", [0, 1])
 @pytest.mark.parametrize("kind", ["tucker", "cp"])
-def test_graph_replay_factorized(kind, policy, separate):
+def test_graph_replay_factorized(kind, policy, separate, forked):
     """separate: the backward as bwd_data (keeping the gradient spectrum) and
     bwd_weight from the two spectra, instead of the combined call."""
-    n, modes, Bt, ci, co, rank = FACTOR_CASES[kind]
+    n, modes, Bt, ci, co, rank = (FORKED_CASES if forked else FACTOR_CASES)[kind]
     prec = "fp16_tanh"
     _, npdt, oprec = U.prec_codes(prec)
     U.say(f"graph replay {kind} policy {policy}: n={n} modes={modes} B={Bt} C={ci}->{co} "

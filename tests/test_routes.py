@@ -126,3 +126,53 @@ def test_products_per_thread(tmp_path):
   bad += !four_products_pay(8388608, 1, 8);
   bad += four_products_pay(2097152, 1, 1) || four_products_pay(33554432, 1, 1);
   return bad;""")
+
+
+def test_forks_of_factorised_calls(tmp_path):
+    """Calls on either side of the lines as measured: each way in us, forked and
+    on one stream."""
+    replay(tmp_path, """
+  int bad = 0;
+  auto expect = [&](bool cp, bool fp16, bool gen, int nd, long pts, int nb, int kbp, long modes,
+                    int b, int ci, int co, int r0, int r1, ForkCall call, bool rec, bool want) {
+    FactorShape f{cp, fp16, gen, nd, pts * b * (ci + co), nb, kbp,
+                  modes * b * (ci * r0 + co * r1), cp ? 0 : modes * r0 * r1};
+    if (fork_pays(f, call, rec) != want)
+      ++bad, std::printf("%d %d %d %d %d\\n", nd, nb, (int)modes, (int)call, rec);
+  };
+  // 114 x 216, 22 x 91 modes, rank 9 x 8: recorded 163, 229
+  expect(0, 1, 1, 2, 114 * 216, 216, 128, 2002, 1, 12, 26, 9, 8, FORK_BACKWARD, 1, true);
+  // 175 x 46, 100 x 14 modes, rank 3 x 34: recorded 142, 196, launched 249, 199
+  expect(0, 1, 0, 2, 175 * 46, 46, 16, 1400, 4, 26, 114, 3, 34, FORK_BACKWARD, 1, true);
+  expect(0, 1, 0, 2, 175 * 46, 46, 16, 1400, 4, 26, 114, 3, 34, FORK_BACKWARD, 0, false);
+  // 965 points in fp32, 25 modes, rank 22 x 8: recorded 198, 248, launched 239, 264
+  expect(0, 0, 1, 1, 965, 965, 32, 25, 5, 35, 118, 22, 8, FORK_BACKWARD, 1, true);
+  expect(0, 0, 1, 1, 965, 965, 32, 25, 5, 35, 118, 22, 8, FORK_BACKWARD, 0, true);
+  // 125 x 390, 40 x 128 modes, rank 21 x 5: launched 393, 455; weight gradient 167, 141
+  expect(0, 1, 1, 2, 125 * 390, 390, 128, 5120, 2, 25, 14, 21, 5, FORK_BACKWARD, 0, true);
+  expect(0, 1, 1, 2, 125 * 390, 390, 128, 5120, 2, 25, 14, 21, 5, FORK_WGRAD, 0, false);
+  // 128 x 128, 64 x 32 modes, CP rank 16, 32 samples of 64 channels: launched 212, 170,
+  // recorded 155, 167; weight gradient 125, 78
+  expect(1, 1, 0, 2, 128 * 128, 128, 32, 2048, 32, 64, 64, 16, 16, FORK_BACKWARD, 0, false);
+  expect(1, 1, 0, 2, 128 * 128, 128, 32, 2048, 32, 64, 64, 16, 16, FORK_BACKWARD, 1, true);
+  expect(1, 1, 0, 2, 128 * 128, 128, 32, 2048, 32, 64, 64, 16, 16, FORK_WGRAD, 0, false);
+  // 256 x 256, 64 x 32 modes, rank 13 x 13, 16 samples of 128 channels: launched 374, 472,
+  // recorded 342, 469; forward 227, 242
+  for (bool rec : {false, true}) {
+    expect(0, 1, 0, 2, 65536, 256, 32, 2048, 16, 128, 128, 13, 13, FORK_BACKWARD, rec, true);
+    expect(0, 1, 0, 2, 65536, 256, 32, 2048, 16, 128, 128, 13, 13, FORK_PATH, rec, true);
+  }
+  // 8 x 160, 6 x 70 modes, 10 samples of 26 to 24 channels (the recorded calls of the
+  // GPU test of graphs)
+  for (bool cp : {false, true}) {
+    expect(cp, 1, 1, 2, 1280, 160, 128, 420, 10, 26, 24, 8, 6, FORK_BACKWARD, 1, true);
+    expect(cp, 1, 1, 2, 1280, 160, 128, 420, 10, 26, 24, 8, 6, FORK_PATH, 1, !cp);
+    expect(cp, 1, 1, 2, 1280, 160, 128, 420, 10, 26, 24, 8, 6, FORK_BACKWARD, 0, false);
+  }
+  // few points: on one stream
+  for (ForkCall c : {FORK_PATH, FORK_BACKWARD, FORK_WGRAD})
+    for (bool rec : {false, true}) {
+      expect(0, 1, 0, 1, 256, 256, 16, 16, 8, 16, 16, 4, 4, c, rec, false);
+      expect(1, 1, 0, 2, 64 * 64, 64, 16, 512, 2, 16, 16, 8, 8, c, rec, false);
+    }
+  return bad;""")
