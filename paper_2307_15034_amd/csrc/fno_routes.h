@@ -53,6 +53,10 @@ constexpr bool any_extents_fit(int64_t Na, int64_t Nb) {
 // 264: 23.6 and 28.7, of 49 x 105: 27.6 and 22.4, 2048 of 200 x 16: 57 and 64;
 // fp32 forward, 256 planes of 30 x 200: 32.3 and 36.6, 512 of 32 x 504: 73.6 and
 // 65.4; inverse, 256 of 48 x 73 with 28 modes: 35.0 and 31.1.
+// Forward fp32 planes of odd rows with 33 to 64 modes (unfolded, in segments of 32
+// columns) of at most two blocks have a line of their own up to one plane per compute
+// unit: the generic kernel was quicker in all 191 measured, by 3 to 22 us (4 planes of
+// 20 x 383, 44 modes, whole call 91 and 105 us), and slower in the 42 of 65 to 100 rows.
 constexpr bool few_small_planes(const PlaneShape& g, bool inverse) {
   typedef const short Lines[2][4][5];  // [aligned rows][blocks][planes per unit]: work / 16
   constexpr Lines h_fwd = {
@@ -71,6 +75,7 @@ constexpr bool few_small_planes(const PlaneShape& g, bool inverse) {
   if (units < 1 || units > 12) return false;
   const int q = units < 5 ? (int)units - 1 : 4;
   const int b = g.Na <= 32 ? 0 : g.Na <= 64 ? 1 : g.Na <= 128 ? 2 : 3;
+  if (!g.fp16 && !inverse && g.Nb % 2 && g.Kbp == 64 && b <= 1 && units == 1) return true;
   const bool aligned = g.Nb % (g.fp16 ? 8 : 4) == 0;
   const Lines& l = g.fp16 ? (inverse ? h_inv : h_fwd) : (inverse ? s_inv : s_fwd);
   return (g.Na + 15) / 16 * (int64_t)g.Nb * (g.Kbp / 16) <= l[aligned][b][q];

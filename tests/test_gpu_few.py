@@ -30,6 +30,8 @@ CASES = [
     ((15, 43), (5, 5), 1, 16, 16, "fp16", "r2c_plane_kernel", "c2r_plane_kernel"),
     ((24, 24), (4, 5), 2, 16, 16, "fp32", "r2c_plane_kernel", "c2r_plane_kernel"),
     ((30, 200), (3, 5), 1, 16, 16, "fp32", "r2c_plane_kernel", None),
+    ((19, 131), (4, 35), 1, 4, 3, "fp32", "r2c_plane_kernel", "c2r_any32_kernel"),
+    ((64, 129), (10, 64), 2, 3, 3, "fp32", "r2c_plane_kernel", "c2r_any32_kernel"),
     ((64,), (5,), 2, 16, 16, "fp16", "r2c_fast_kernel<2, 2, 4>", "c2r_line_kernel"),
     ((128,), (18,), 2, 16, 16, "fp16", "r2c_fast_kernel<4, 4, 4>", "c2r_line_kernel"),
     ((50,), (7,), 2, 16, 16, "fp16", "r2c_plane_kernel", "c2r_line_kernel"),

@@ -64,6 +64,12 @@ def test_few_planes_and_signals(tmp_path):
   expect("fp32 32 x 504, 512", few_small_planes({32, 504, 16, false, 512, 256}, false), false);
   expect("fp32 48 x 73, 256", few_small_planes({48, 73, 32, false, 256, 256}, true), false);
   expect("fp32 128 x 128, 2048", few_small_planes({128, 128, 32, false, 2048, 256}, true), false);
+  expect("fp32 20 x 383, 4", few_small_planes({20, 383, 64, false, 4, 256}, false), true);
+  expect("fp32 64 x 187, 256", few_small_planes({64, 187, 64, false, 256, 256}, false), true);
+  expect("fp32 64 x 187, 257", few_small_planes({64, 187, 64, false, 257, 256}, false), false);
+  expect("fp32 20 x 386, 4", few_small_planes({20, 386, 64, false, 4, 256}, false), false);
+  expect("fp32 70 x 383, 4", few_small_planes({70, 383, 64, false, 4, 256}, false), false);
+  expect("fp32 20 x 383, 4, inverse", few_small_planes({20, 383, 64, false, 4, 256}, true), false);
   // no count of planes leaves the tables
   for (long planes : {1L, 256L, 257L, 1024L, 1025L, 3072L, 3073L, 1L << 31})
     for (int rows : {1, 32, 33, 64, 65, 128, 129, 65536})
