@@ -26,6 +26,7 @@
 
 #include "../../include/fno_spectral_conv.h"
 #include "fno_device.h"
+#include "fno_routes.h"
 #include "fno_host.h"
 
 namespace fno {
@@ -1143,7 +1144,7 @@ fno_status run_mix(const EpiGeo& g, const char* name, const void* in, int K, con
   a.tiles = g.B * a.ptiles;
   L.es = g.es;
   L.s = s;
-  L.pipe = mix_pipe(g, K, N);
+  L.pipe = mix_pipe(g, K, N) && !(g.P % 8 && few_channels(K, N, g.B * g.P));
   L.fast = mix_fast(g, K, N);
   const hipError_t e = timed_launch(name, s, launch_mix, &L);
   return e == hipSuccess ? FNO_OK : report_hip_error(e, name);

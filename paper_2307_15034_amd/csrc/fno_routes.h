@@ -121,6 +121,16 @@ constexpr bool quad_pays(int64_t M, int64_t N, int64_t K, int64_t waves) {
   return !(waves <= 256 && M <= 64 && N <= 8 && K <= 32);
 }
 
+// The channel mix of fp16 rows whose length is not a multiple of eight, K to N
+// channels of `points`: whether the kernels without matrix cores are quicker.  With
+// so few products the pipelined ones are staging alone (1 to 1 channel, 120002
+// points 8.2 against 4.8 us, 2 to 4 8.3 against 6.3, of 11300 points 5.5 against 5.7),
+// and their 128 columns of weights cost more than a few products of few points (2 to
+// 128, 11300 points 11.2 against 9.9, 57860 24 against 30).
+constexpr bool few_channels(int64_t K, int64_t N, int64_t points) {
+  return K * N <= (points < 32768 ? 6 : 12) || (K <= 4 && N > 64 && points <= 16384);
+}
+
 // Elementwise and outer products of `results` values: four results per thread
 // instead of two.  Only outer products gain, whose operand without the innermost
 // index (stride other than one) is loaded once for the four, and only from about

@@ -24,6 +24,9 @@ CASES = [
     (129, 3, 33, 64, False),   # odd channel counts, two output tiles per wave
     (1225, 4, 128, 128, True),
     (4097, 2, 64, 64, True),
+    (301, 3, 1, 1, True),      # few channels: the kernels without matrix cores
+    (301, 2, 2, 128, False),   # forward so, data gradient pipelined
+    (301, 2, 128, 2, False),   # and the other way round
     # skip weights whose rows are not a multiple of eight, aligned points
     (248, 12, 20, 128, False),  # pieces run over rows, 320 of them
     (64, 2, 1, 1, True),        # less than one piece

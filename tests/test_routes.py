@@ -182,3 +182,14 @@ def test_forks_of_factorised_calls(tmp_path):
       expect(1, 1, 0, 2, 64 * 64, 64, 16, 512, 2, 16, 16, 8, 8, c, rec, false);
     }
   return bad;""")
+
+
+def test_mixes_of_few_channels(tmp_path):
+    """As measured: channels in and out, points."""
+    replay(tmp_path, """
+  int bad = 0;
+  bad += !few_channels(1, 1, 120002) + !few_channels(1, 1, 116) + !few_channels(2, 4, 120002);
+  bad += !few_channels(2, 128, 11300) + !few_channels(4, 128, 2408) + !few_channels(3, 2, 57860);
+  bad += few_channels(2, 128, 57860) + few_channels(8, 20, 116) + few_channels(4, 4, 11300);
+  bad += few_channels(1, 64, 120002) + few_channels(64, 64, 2450) + few_channels(6, 64, 2408);
+  return bad;""")
