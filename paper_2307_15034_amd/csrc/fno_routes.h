@@ -53,6 +53,10 @@ constexpr bool any_extents_fit(int64_t Na, int64_t Nb) {
 // 264: 23.6 and 28.7, of 49 x 105: 27.6 and 22.4, 2048 of 200 x 16: 57 and 64;
 // fp32 forward, 256 planes of 30 x 200: 32.3 and 36.6, 512 of 32 x 504: 73.6 and
 // 65.4; inverse, 256 of 48 x 73 with 28 modes: 35.0 and 31.1.
+// Forward fp16 planes of up to 64 rows and two to four planes per compute unit have
+// their lines from 120 calls with tanh, whose table the kernels for any extents
+// stage: below them these are 0.3 to 1.8 us behind (440 planes of 8 x 18, 3 modes, whole
+// call 19.0 and 20.7), without tanh 0.7 us behind to 0.6 ahead.
 // Forward fp32 planes of odd rows with 33 to 64 modes (unfolded, in segments of 32
 // columns) of at most two blocks have a line of their own up to one plane per compute
 // unit: the generic kernel was quicker in all 191 measured, by 3 to 22 us (4 planes of
@@ -60,8 +64,8 @@ constexpr bool any_extents_fit(int64_t Na, int64_t Nb) {
 constexpr bool few_small_planes(const PlaneShape& g, bool inverse) {
   typedef const short Lines[2][4][5];  // [aligned rows][blocks][planes per unit]: work / 16
   constexpr Lines h_fwd = {
-      {{64, 0, 0, 0, 0}, {128, 0, 0, 0, 0}, {192, 0, 192, 128, 0}, {0, 0, 256, 256, 96}},
-      {{384, 0, 0, 0, 0}, {640, 0, 0, 0, 0}, {192, 0, 256, 192, 192}, {0, 384, 384, 384, 256}}};
+      {{64, 64, 64, 64, 0}, {128, 96, 64, 0, 0}, {192, 0, 192, 128, 0}, {0, 0, 256, 256, 96}},
+      {{384, 384, 384, 96, 0}, {640, 0, 0, 0, 0}, {192, 0, 256, 192, 192}, {0, 384, 384, 384, 256}}};
   constexpr Lines h_inv = {
       {{256, 128, 96, 0, 0}, {256, 128, 64, 0, 0}, {192, 64, 256, 0, 64}, {0, 192, 256, 96, 192}},
       {{1024, 512, 512, 0, 0}, {1536, 640, 192, 0, 64}, {384, 128, 2048, 128, 128}, {0, 256, 384, 256, 256}}};

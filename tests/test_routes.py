@@ -64,6 +64,9 @@ def test_few_planes_and_signals(tmp_path):
   expect("fp32 32 x 504, 512", few_small_planes({32, 504, 16, false, 512, 256}, false), false);
   expect("fp32 48 x 73, 256", few_small_planes({48, 73, 32, false, 256, 256}, true), false);
   expect("fp32 128 x 128, 2048", few_small_planes({128, 128, 32, false, 2048, 256}, true), false);
+  expect("8 x 18, 440", few_small_planes({8, 18, 16, true, 440, 256}, false), true);
+  expect("8 x 18, 1100", few_small_planes({8, 18, 16, true, 1100, 256}, false), false);
+  expect("20 x 60, 600", few_small_planes({20, 60, 32, true, 600, 256}, false), false);
   expect("fp32 20 x 383, 4", few_small_planes({20, 383, 64, false, 4, 256}, false), true);
   expect("fp32 64 x 187, 256", few_small_planes({64, 187, 64, false, 256, 256}, false), true);
   expect("fp32 64 x 187, 257", few_small_planes({64, 187, 64, false, 257, 256}, false), false);
