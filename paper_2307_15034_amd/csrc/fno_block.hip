@@ -16,9 +16,10 @@
 // Channel rows whose length is not a multiple of eight points start at any
 // two-byte address: the pipelined fp16 kernels read and write them with
 // 16-byte accesses at that alignment (RAG; the three calls on 4 x 128 channels of
-// 35 x 35 points took the generic kernels 980 us, these take 69).  Table-free generic kernels cover
-// what the matrix-core kernels do not (wide channel counts, fp32 rows that
-// are not a multiple of eight points).
+// 35 x 35 points took the generic kernels 980 us, these take 69).  Table-free generic
+// kernels cover what the matrix-core kernels do not (wide channel counts, fp32
+// rows that are not a multiple of eight points) and mixes of so few channels that
+// they start sooner (few_channels).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
